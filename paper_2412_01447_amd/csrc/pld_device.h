@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
 #error "this library is written for gfx950 (MI355X) only"
@@ -47,7 +48,7 @@ inline int resident_blocks(const void *kernel, int threads, size_t dyn_lds) {
         int blocks;
     };
     static std::mutex mu;
-    static Entry cache[64];
+    static Entry cache[256];
     static int used = 0;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
@@ -66,7 +67,7 @@ inline int resident_blocks(const void *kernel, int threads, size_t dyn_lds) {
         per = 1;
     const int blocks = cus * per;
     std::lock_guard<std::mutex> g(mu);
-    if (used < 64) cache[used++] = Entry{dev, kernel, dyn_lds, blocks};
+    if (used < 256) cache[used++] = Entry{dev, kernel, dyn_lds, blocks};
     return blocks;
 }
 
@@ -307,10 +308,7 @@ __device__ __forceinline__ void finish_row(const float (&ad)[4], const float (&a
     nrm = wave_sum_f32((an[0] + an[1]) + (an[2] + an[3]));
 }
 
-// One row of any width: up to 16 chunks per lane requested at once.  `row`
-// is either the LDS copy of the query (kStream false) or a candidate row in
-// HBM read once (kStream true).
-template <bool kStream>
+// One candidate row of any width: up to 16 chunks per lane requested at once.
 __device__ __forceinline__ void row_dot(const uint4 *row, const uint4 *q, int nch, float &dot,
                                         float &nrm) {
     constexpr int U = 16;
@@ -321,7 +319,7 @@ __device__ __forceinline__ void row_dot(const uint4 *row, const uint4 *q, int nc
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int ch = c0 + u * kWave;
-            if (ch < nch) v[u] = kStream ? ld_stream(row + ch) : row[ch];
+            if (ch < nch) v[u] = ld_stream(row + ch);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -346,92 +344,153 @@ __device__ __forceinline__ float query_norm(const uint4 *q, int nch) {
     return nrm;
 }
 
-// G rows of width nch <= 64 * (16 / G) chunks, all their loads requested at
-// once; a row whose pointer is null is skipped (its results are 0).
-template <int G>
-__device__ __forceinline__ void rows_dot(const uint4 *const (&rows)[G], const uint4 *q, int nch,
-                                         float (&dot)[G], float (&nrm)[G]) {
-    constexpr int U = 16 / G;
-    const int lane = lane_id();
-    uint4 v[G][U];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int ch = lane + u * kWave;
-            if (rows[g] && ch < nch) v[g][u] = ld_stream(rows[g] + ch);
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        float ad[4] = {0.f, 0.f, 0.f, 0.f}, an[4] = {0.f, 0.f, 0.f, 0.f};
-        if (rows[g]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int ch = lane + u * kWave;
-                if (ch < nch) accum_chunk(v[g][u], q[ch], ad, an);
-            }
-        }
-        finish_row(ad, an, dot[g], nrm[g]);
-    }
-}
-
-// Rows streamed through a two-deep pipeline of pieces.  A piece is 64 kU
-// chunks of 8 bf16 (kU 16-byte loads per lane, lane l taking chunks l, l+64,
-// ... of the piece; 4 KB for kU = 4); a row is kPieces pieces.  The callers
-// split a row in two (kPieces = 2: kU = 4 for d = 4096, 8 for d = 8192), the
-// fastest of the piece sizes measured for both widths.
-// The wave keeps the loads of the next piece in flight while it reduces the
-// current one, so its memory queue never drains between rows the way a
-// load-all-then-wait round does.  The accumulation order is row_dot's (lane l
-// visits its chunks l, l+64, l+128, ... in order, pair p of a chunk into
-// acc[p]), so a row gives the same bits here as through row_dot / rows_dot.
+// Candidate rows streamed through a two-deep pipeline of pieces: the wave keeps
+// the loads of the next piece in flight while it reduces the current one, so
+// its memory queue never drains the way a load-all-then-wait round does.  Rows
+// have up to 64 kLoads chunks of 8 bf16, kLoads 16-byte loads per lane of which
+// only the last can be short (masked by chunk).  A piece is kRows whole rows
+// (kRows > 0) or half a row (kRows = 0).  with_row_form picks the form.
+// The accumulation order is row_dot's (lane l visits its chunks l, l+64,
+// l+128, ... in order, pair p of a chunk into acc[p]), so a row gives the same
+// bits here as through row_dot.
 // `row(k)` gives the k-th row (k < n) of this wave, or null for an unusable
 // one (its results are reported as not valid); `done(k, valid, dot, nrm)` runs
 // in every lane when row k is complete, in order of k.
-template <int kPieces, int kU, class RowPtr, class Done>
-__device__ __forceinline__ void stream_rows(int n, RowPtr row, const uint4 *q, Done done) {
-    constexpr int kPiece = kU * kWave;    // chunks per piece (kU 16-byte loads per lane)
+template <int kRows, int kLoads, class RowPtr, class Done>
+__device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const uint4 *q,
+                                            Done done) {
     const int lane = lane_id();
-    const int total = n * kPieces;
-    uint4 buf[2][kU];
-    float ad[4] = {0.f, 0.f, 0.f, 0.f}, an[4] = {0.f, 0.f, 0.f, 0.f};
-    auto issue = [&](int slot, int pc) {
-        const uint4 *r = row(pc / kPieces);
-        if (r) {
-            const uint4 *src = r + (pc % kPieces) * kPiece + lane;
+    auto has = [&](int u) { return u < kLoads - 1 || u * kWave + lane < nch; };
+    constexpr std::integral_constant<int, 0> first{};
+    constexpr std::integral_constant<int, 1> second{};
+    if constexpr (kRows > 0) {
+        uint4 buf[2][kRows][kLoads];
+        auto issue = [&](auto slot, int k0) {
+            constexpr int sl = decltype(slot)::value;
 #pragma unroll
-            for (int u = 0; u < kU; ++u) buf[slot][u] = ld_stream(src + u * kWave);
-        }
-    };
-    auto consume = [&](int slot, int pc) {
-        const int k = pc / kPieces, p = pc % kPieces;
-        const bool ok = row(k) != nullptr;
-        if (p == 0) {
+            for (int g = 0; g < kRows; ++g) {
+                const uint4 *r = k0 + g < n ? row(k0 + g) : nullptr;
+                if (r) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ad[i] = an[i] = 0.f;
-        }
-        if (ok) {
-            const uint4 *qq = q + p * kPiece + lane;
+                    for (int u = 0; u < kLoads; ++u)
+                        if (has(u)) buf[sl][g][u] = ld_stream(r + lane + u * kWave);
+                }
+            }
+        };
+        auto consume = [&](auto slot, int k0) {
+            constexpr int sl = decltype(slot)::value;
+            float dot[kRows], nrm[kRows];
+            bool ok[kRows];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) accum_chunk(buf[slot][u], qq[u * kWave], ad, an);
+            for (int g = 0; g < kRows; ++g) {
+                float ad[4] = {0.f, 0.f, 0.f, 0.f}, an[4] = {0.f, 0.f, 0.f, 0.f};
+                ok[g] = k0 + g < n && row(k0 + g) != nullptr;
+                if (ok[g]) {
+#pragma unroll
+                    for (int u = 0; u < kLoads; ++u)
+                        if (has(u)) accum_chunk(buf[sl][g][u], q[lane + u * kWave], ad, an);
+                }
+                finish_row(ad, an, dot[g], nrm[g]);
+            }
+#pragma unroll
+            for (int g = 0; g < kRows; ++g)
+                if (k0 + g < n) done(k0 + g, ok[g], dot[g], nrm[g]);
+        };
+        issue(first, 0);
+        issue(second, kRows);
+        for (int k = 0; k < n; k += 2 * kRows) {
+            consume(first, k);
+            issue(first, k + 2 * kRows);
+            if (k + kRows < n) {
+                consume(second, k + kRows);
+                issue(second, k + 3 * kRows);
+            }
         }
-        if (p == kPieces - 1) {
-            float dot, nrm;
-            finish_row(ad, an, dot, nrm);
-            done(k, ok, dot, nrm);
+    } else {
+        constexpr int kHalf = (kLoads + 1) / 2;      // loads of piece 0
+        uint4 buf[2][kHalf];
+        float ad[4] = {0.f, 0.f, 0.f, 0.f}, an[4] = {0.f, 0.f, 0.f, 0.f};
+        auto issue = [&](auto piece, int k) {
+            constexpr int p = decltype(piece)::value;
+            const uint4 *r = row(k);
+            if (r) {
+#pragma unroll
+                for (int u = 0; u < kHalf && p * kHalf + u < kLoads; ++u)
+                    if (has(p * kHalf + u))
+                        buf[p][u] = ld_stream(r + lane + (p * kHalf + u) * kWave);
+            }
+        };
+        auto consume = [&](auto piece, int k) {
+            constexpr int p = decltype(piece)::value;
+            const bool ok = row(k) != nullptr;
+            if (p == 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ad[i] = an[i] = 0.f;
+            }
+            if (ok) {
+#pragma unroll
+                for (int u = 0; u < kHalf && p * kHalf + u < kLoads; ++u)
+                    if (has(p * kHalf + u))
+                        accum_chunk(buf[p][u], q[lane + (p * kHalf + u) * kWave], ad, an);
+            }
+            if (p == 1) {
+                float dot, nrm;
+                finish_row(ad, an, dot, nrm);
+                done(k, ok, dot, nrm);
+            }
+        };
+        if (n > 0) {
+            issue(first, 0);
+            issue(second, 0);
         }
-    };
-    if (total > 0) issue(0, 0);
-    if (total > 1) issue(1, 1);
-    for (int pc = 0; pc < total; pc += 2) {
-        consume(0, pc);
-        if (pc + 2 < total) issue(0, pc + 2);
-        if (pc + 1 < total) {
-            consume(1, pc + 1);
-            if (pc + 3 < total) issue(1, pc + 3);
+        for (int k = 0; k < n; ++k) {
+            consume(first, k);
+            if (k + 1 < n) issue(first, k + 1);
+            consume(second, k);
+            if (k + 1 < n) issue(second, k + 1);
         }
     }
+}
+
+// Calls f(integral_constant<kRows>, integral_constant<kLoads>) with the form
+// in which rows of width d stream, or (0, 0) past 8192 (row_dot, one row at a
+// time).  A piece holds about eight loads per lane for narrow rows, else a whole
+// row, up to twelve loads: past that two pieces no longer fit the 128 registers
+// that keep four waves per SIMD (two 8-wave blocks per CU), and half a row is a
+// piece.  Measured as one-call
+// drafting of 8 x 65536 tokens with 1600 occurrences each (us per step, whole
+// rows | half rows | all loads of one to four rows, then a wait): d = 512
+// 23.0 | - | 24.5, 1024 25.0 | - | 25.5, 2048 28.9 | - | 28.8, 3584 35.1 | - |
+// 35.6, 4096 37.2 | 40.4 | -, 5120 41.6 | 43.6 | 43.5, 6144 47.5 | 47.9 | 48.3,
+// 7168 51.3 | 53.2 | 53.0, 8192 55.8 | 56.0 | -; but 44 x 16917 tokens with few
+// occurrences, d = 7168, take 39.2 | 35.6 | 35.6, the blocks no longer resident
+// together.  Half again as many narrow rows per
+// piece: the same or up to 1 us slower.
+template <class F>
+inline void with_row_form(int d, F f) {
+    using std::integral_constant;
+#define PLD_ROW_FORM(rows, loads) \
+    return f(integral_constant<int, rows>{}, integral_constant<int, loads>{})
+    switch ((d + 511) / 512) {   // 16-byte loads per lane and row
+    case 1: PLD_ROW_FORM(8, 1);
+    case 2: PLD_ROW_FORM(4, 2);
+    case 3: PLD_ROW_FORM(2, 3);
+    case 4: PLD_ROW_FORM(2, 4);
+    case 5: PLD_ROW_FORM(1, 5);
+    case 6: PLD_ROW_FORM(1, 6);
+    case 7: PLD_ROW_FORM(1, 7);
+    case 8: PLD_ROW_FORM(1, 8);
+    case 9: PLD_ROW_FORM(1, 9);
+    case 10: PLD_ROW_FORM(1, 10);
+    case 11: PLD_ROW_FORM(1, 11);
+    case 12: PLD_ROW_FORM(1, 12);
+    case 13: PLD_ROW_FORM(0, 13);
+    case 14: PLD_ROW_FORM(0, 14);
+    case 15: PLD_ROW_FORM(0, 15);
+    case 16: PLD_ROW_FORM(0, 16);
+    default: PLD_ROW_FORM(0, 0);
+    }
+#undef PLD_ROW_FORM
 }
 
 // Aggregated attention of one candidate (Eq. 3 / Sec. 7.1), gathered by a

@@ -229,12 +229,12 @@ __global__ __launch_bounds__(256) void select_draft_kernel(SelectDraftArgs a) {
 }
 
 // ---------------------------------------------------------------- hidden
-// Scores the rows i = first, first + kRankWaves, ... < end of sequence b (one
-// wave's share of a segment).  The wave fetches the candidate positions of up
-// to 64 rows with one load (the first batch, jv0, comes in prefetched), then
-// scores G rows at a time with all their loads in flight.  `best` collects the
-// wave's best key.
-template <int G, int kW>
+// Scores the rows i = first, first + kW, ... < end of sequence b (one wave's
+// share of a segment), through the pipeline of their form (stream_rows) or one
+// by one.  The wave fetches the candidate positions of up to 64 rows with one
+// load (the first batch, jv0, comes in prefetched).  `best` collects the wave's
+// best key.
+template <int kRows, int kLoads, int kW>
 __device__ void score_rows(const RankHiddenArgs &a, int b, int64_t T, bool seq_ok,
                            const uint16_t *Hb, const uint4 *q_s, float qq, uint32_t first,
                            uint32_t end, uint32_t seq_start, int32_t jv0, uint64_t &best) {
@@ -248,63 +248,12 @@ __device__ void score_rows(const RankHiddenArgs &a, int b, int64_t T, bool seq_o
         int32_t jv = jv0;   // the first batch was requested with the query row
         if (base > 0 && mine < n)
             jv = c.cand_pos[(int64_t)b * c.cap + (first + mine * kW - seq_start)];
-        for (uint32_t r = 0; r < nb; r += G) {
-            const uint4 *rows[G];
-            int32_t js[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                js[g] = (r + g < nb) ? __builtin_amdgcn_readlane(jv, r + g) : 0;
-                const bool ok = (r + g < nb) && seq_ok && js[g] >= 1 && (int64_t)js[g] <= T - 2;
-                rows[g] = ok ? reinterpret_cast<const uint4 *>(Hb + (int64_t)(js[g] - 1) * a.hr)
-                             : nullptr;
-            }
-            float dot[G], nrm[G];
-            if (G == 1 && nch > 16 * kWave) {
-                if (rows[0]) row_dot<true>(rows[0], q_s, nch, dot[0], nrm[0]);
-            } else {
-                rows_dot<G>(rows, q_s, nch, dot, nrm);
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (r + g >= nb) break;
-                float s = __builtin_nanf("");
-                if (rows[g]) {
-                    s = cosine(dot[g], nrm[g], qq);
-                    if (s > c.threshold) {
-                        const uint64_t k = rank_key(s, js[g]);
-                        best = k > best ? k : best;
-                    }
-                }
-                if (c.scores && lane == 0)
-                    c.scores[(int64_t)b * c.cap +
-                             (first + (base + r + g) * kW - seq_start)] = s;
-            }
-        }
-    }
-}
-
-// The same for rows of d = 1024 * kU: the wave's rows stream through
-// stream_rows' two-deep pipeline, two pieces per row (same bits as score_rows).
-template <int kU, int kW>
-__device__ void score_rows_stream(const RankHiddenArgs &a, int b, int64_t T, bool seq_ok,
-                                  const uint16_t *Hb, const uint4 *q_s, float qq, uint32_t first,
-                                  uint32_t end, uint32_t seq_start, int32_t jv0, uint64_t &best) {
-    const RankCommon &c = a.c;
-    const int lane = lane_id();
-    const uint32_t n = end > first ? (end - first + kW - 1) / kW : 0;
-    for (uint32_t base = 0; base < n; base += kWave) {
-        const uint32_t nb = min((uint32_t)kWave, n - base);
-        const uint32_t mine = base + lane;
-        int32_t jv = jv0;   // the first batch was requested with the query row
-        if (base > 0 && mine < n)
-            jv = c.cand_pos[(int64_t)b * c.cap + (first + mine * kW - seq_start)];
         auto row = [&](int k) -> const uint4 * {
             const int32_t j = __builtin_amdgcn_readlane(jv, k);
             const bool ok = seq_ok && j >= 1 && (int64_t)j <= T - 2;
             return ok ? reinterpret_cast<const uint4 *>(Hb + (int64_t)(j - 1) * a.hr) : nullptr;
         };
-        stream_rows<2, kU>((int)nb, row, q_s,
-                                            [&](int k, bool ok, float dot, float nrm) {
+        auto done = [&](int k, bool ok, float dot, float nrm) {
             float s = __builtin_nanf("");
             if (ok) {
                 s = cosine(dot, nrm, qq);
@@ -315,14 +264,24 @@ __device__ void score_rows_stream(const RankHiddenArgs &a, int b, int64_t T, boo
             }
             if (c.scores && lane == 0)
                 c.scores[(int64_t)b * c.cap + (first + (base + k) * kW - seq_start)] = s;
-        });
+        };
+        if constexpr (kLoads > 0) {
+            stream_rows<kRows, kLoads>((int)nb, nch, row, q_s, done);
+        } else {
+            for (int k = 0; k < (int)nb; ++k) {
+                const uint4 *r = row(k);
+                float dot = 0.f, nrm = 0.f;
+                if (r) row_dot(r, q_s, nch, dot, nrm);
+                done(k, r != nullptr, dot, nrm);
+            }
+        }
     }
 }
 
 // Block k of g of the hidden-state ranking (its share of the flattened
 // list).  smem: the query row (d/8 chunks), then pre (B + 1) and the lengths
 // (B); s_best: kW words.
-template <int kU, int kW>
+template <int kRows, int kLoads, int kW>
 __device__ void hidden_block(const RankHiddenArgs &a, uint32_t k, uint32_t g, uint4 *smem,
                              uint64_t *s_best) {
     const RankCommon &c = a.c;
@@ -354,15 +313,8 @@ __device__ void hidden_block(const RankHiddenArgs &a, uint32_t k, uint32_t g, ui
         __syncthreads();
         const float qq = seq_ok ? query_norm(q_s, nch) : 0.f;
         uint64_t best = 0;
-        if constexpr (kU > 0)
-            score_rows_stream<kU, kW>(a, b, T, seq_ok, Hb, q_s, qq, first, seg_hi, pre[b], jv0,
-                                       best);
-        else if (nch <= 4 * kWave)
-            score_rows<4, kW>(a, b, T, seq_ok, Hb, q_s, qq, first, seg_hi, pre[b], jv0, best);
-        else if (nch <= 8 * kWave)
-            score_rows<2, kW>(a, b, T, seq_ok, Hb, q_s, qq, first, seg_hi, pre[b], jv0, best);
-        else
-            score_rows<1, kW>(a, b, T, seq_ok, Hb, q_s, qq, first, seg_hi, pre[b], jv0, best);
+        score_rows<kRows, kLoads, kW>(a, b, T, seq_ok, Hb, q_s, qq, first, seg_hi, pre[b], jv0,
+                                      best);
         if (lane == 0) s_best[w] = best;
         __syncthreads();                                       // also: q_s is restaged next
         if (threadIdx.x == 0) {
@@ -376,14 +328,13 @@ __device__ void hidden_block(const RankHiddenArgs &a, uint32_t k, uint32_t g, ui
     }
 }
 
-// kU > 0: rows of d = 1024 * kU through the streaming pipeline; 0: any d
-// through score_rows (one instantiation per path keeps each kernel's register
-// count to what its path needs).
-template <int kU, int kW>
+// One instantiation per form of the rows keeps each kernel's register count to
+// what its form needs.
+template <int kRows, int kLoads, int kW>
 __global__ __launch_bounds__(kW * kWave) void rank_hidden_kernel(RankHiddenArgs a) {
     extern __shared__ uint4 smem[];
     __shared__ uint64_t s_best[kW];
-    hidden_block<kU, kW>(a, blockIdx.x, gridDim.x, smem, s_best);
+    hidden_block<kRows, kLoads, kW>(a, blockIdx.x, gridDim.x, smem, s_best);
 }
 
 // ------------------------------------------------------------------ attn
@@ -453,7 +404,7 @@ __global__ __launch_bounds__(kRankThreads) void rank_attn_kernel(RankAttnArgs a)
 // bit).  The attention gathers then overlap the stream of hidden rows instead
 // of following it in a launch of their own.  ga is a multiple of 8, so the
 // attention blocks' XCD runs line up with the hardware's round-robin.
-template <int kU>
+template <int kRows, int kLoads>
 __global__ __launch_bounds__(kRankThreads) void rank_both_kernel(RankHiddenArgs h, RankAttnArgs t,
                                                                  uint32_t ga) {
     extern __shared__ uint4 smem[];
@@ -461,7 +412,7 @@ __global__ __launch_bounds__(kRankThreads) void rank_both_kernel(RankHiddenArgs 
     if (blockIdx.x < ga)   // block-uniform
         attn_block(t, blockIdx.x, ga, reinterpret_cast<uint32_t *>(smem));
     else
-        hidden_block<kU, kRankWaves>(h, blockIdx.x - ga, gridDim.x - ga, smem, s_best);
+        hidden_block<kRows, kLoads, kRankWaves>(h, blockIdx.x - ga, gridDim.x - ga, smem, s_best);
 }
 
 static RankCommon make_common(const int32_t *lens, const int32_t *cand_pos, int64_t cap,
@@ -527,21 +478,15 @@ static int prep_attn(const float *attn, int64_t a_seq_stride, int64_t a_row_stri
 
 // The ranking grids are persistent: as many blocks as fit on the device at
 // once, each taking an equal contiguous share of the flattened candidates.
-template <int kU, int kW>
-static void launch_hidden_as(const RankHiddenArgs &a, size_t lds, hipStream_t s) {
-    const void *k = reinterpret_cast<const void *>(&rank_hidden_kernel<kU, kW>);
-    const int grid = resident_blocks(k, kW * kWave, lds) * PLD_RANK_OVERSUB;
-    hipLaunchKernelGGL((rank_hidden_kernel<kU, kW>), dim3(grid), dim3(kW * kWave), lds, s, a);
-}
-
 static void launch_hidden(const RankHiddenArgs &a, hipStream_t s) {
     const size_t lds = (size_t)(a.d / 8) * sizeof(uint4) + (size_t)(2 * a.c.B + 1) * sizeof(uint32_t);
-    if (a.d == 4096)
-        launch_hidden_as<4, kRankWaves>(a, lds, s);
-    else if (a.d == 8192)
-        launch_hidden_as<8, kRankWaves>(a, lds, s);
-    else
-        launch_hidden_as<0, kRankWaves>(a, lds, s);
+    with_row_form(a.d, [&](auto rows, auto loads) {
+        constexpr auto kernel = &rank_hidden_kernel<decltype(rows)::value, decltype(loads)::value,
+                                                    kRankWaves>;
+        const int grid = resident_blocks(reinterpret_cast<const void *>(kernel), kRankThreads, lds) *
+                         PLD_RANK_OVERSUB;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kRankThreads), lds, s, a);
+    });
 }
 
 #ifndef PLD_BOTH_ATTN_PERMILLE
@@ -552,25 +497,16 @@ static void launch_hidden(const RankHiddenArgs &a, hipStream_t s) {
 // them (a multiple of 8) rank by attention, the rest by hidden states.  On the
 // 64 x 16384 workload (1024 resident blocks) 192 to 224 attention blocks
 // were equally fast, 208 in the middle.
-template <int kU>
-static void launch_both_as(const RankHiddenArgs &h, const RankAttnArgs &t, size_t lds,
-                           hipStream_t s) {
-    const void *k = reinterpret_cast<const void *>(&rank_both_kernel<kU>);
-    const int grid = resident_blocks(k, kRankThreads, lds);
-    uint32_t ga = (uint32_t)((int64_t)grid * PLD_BOTH_ATTN_PERMILLE / 1000) / 8 * 8;
-    if (ga < 8) ga = 8;
-    const unsigned total = (unsigned)(grid > (int)ga ? grid : (int)ga + 8);
-    hipLaunchKernelGGL((rank_both_kernel<kU>), dim3(total), dim3(kRankThreads), lds, s, h, t, ga);
-}
-
 static void launch_both(const RankHiddenArgs &h, const RankAttnArgs &t, hipStream_t s) {
     const size_t lds = (size_t)(h.d / 8) * sizeof(uint4) + (size_t)(2 * h.c.B + 1) * sizeof(uint32_t);
-    if (h.d == 4096)
-        launch_both_as<4>(h, t, lds, s);
-    else if (h.d == 8192)
-        launch_both_as<8>(h, t, lds, s);
-    else
-        launch_both_as<0>(h, t, lds, s);
+    with_row_form(h.d, [&](auto rows, auto loads) {
+        constexpr auto kernel = &rank_both_kernel<decltype(rows)::value, decltype(loads)::value>;
+        const int grid = resident_blocks(reinterpret_cast<const void *>(kernel), kRankThreads, lds);
+        uint32_t ga = (uint32_t)((int64_t)grid * PLD_BOTH_ATTN_PERMILLE / 1000) / 8 * 8;
+        if (ga < 8) ga = 8;
+        const unsigned total = (unsigned)(grid > (int)ga ? grid : (int)ga + 8);
+        hipLaunchKernelGGL(kernel, dim3(total), dim3(kRankThreads), lds, s, h, t, ga);
+    });
 }
 
 static void launch_attn(const RankAttnArgs &a, hipStream_t s) {

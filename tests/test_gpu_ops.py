@@ -291,6 +291,42 @@ def test_rank_hidden_parity(d):
     say("near-tie flips", flips)
 
 
+@pytest.mark.parametrize("d", [8, 504, 512, 520, 1024, 1032, 1536, 1544, 2048, 2056, 2568, 3072, 3080,
+                               3584, 4088, 4096, 4104, 4616, 5120, 5128, 5640, 6152, 6656, 6664,
+                               7168, 7680, 7688, 8184, 8192, 8200])
+def test_rank_hidden_row_load_edges(d):
+    """Row widths at the edges of the streamed rows' forms (one to sixteen loads per
+    lane, eight rows to half a row per piece, the last load full or short, and the
+    first width that does not stream): the separate call and the one-call drafting
+    give the same bits, within 1e-5 of the oracle (an fp32 sum of at most 8200
+    products of unit variance over norms of order sqrt(d): errors of order eps),
+    with every row followed by NaN, which a load past the row's end would carry
+    into the score."""
+    say("row loads d", d)
+    B, T, K, pad = 4, 400, 5, 8
+    toks, lens, bits, cp, cc = _hidden_case(B, T, d, 9, d, row_pad=pad)
+    bits[:, :, d:] = 0x7fc0
+    hd = d_bf16(bits)[:, :, :d]
+    rsc, rbp, rbs = oracle.rank_hidden(np.ascontiguousarray(bits[:, :, :d]), lens, cp, cc)
+    gsc, gbp, gbs = gpu_rank_hidden(hd, lens, cp, cc)
+    check_best(gbp, gbs, rsc, rbp, rbs, cp, cc, f"d={d}")
+    for b in range(B):
+        assert np.abs(gsc[b, :cc[b]] - rsc[b, :cc[b]]).max(initial=0) <= 1e-5
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for S in (1, 3):
+        o = [torch.full((B, T), -1, **i32), torch.zeros(B, **i32), torch.zeros(B, **i32),
+             torch.zeros(B, **i32), torch.zeros(B, dtype=torch.float32, device="cuda"),
+             torch.zeros((B, K), **i32), torch.zeros(B, **i32)]
+        sc = torch.zeros((B, T), dtype=torch.float32, device="cuda")
+        pld.pld_draft_hidden(d_i32(toks), d_i32(lens), 1, 1, hd, K, *o, scores=sc,
+                             blocks_per_seq=S, workspace=draft_workspace(B, S))
+        torch.cuda.synchronize()
+        gs = sc.cpu().numpy()
+        for b in range(B):
+            assert np.array_equal(gs[b, :cc[b]], gsc[b, :cc[b]])
+        assert np.array_equal(o[3].cpu().numpy(), gbp)
+
+
 def test_rank_at_the_largest_batch_and_width():
     """B = PLD_MAX_BATCH sequences with hidden rows of the largest width
     (PLD_MAX_HIDDEN): every ranking block holds the per-sequence prefix of all
