@@ -256,6 +256,16 @@ __device__ __forceinline__ uint4 ld_stream(const uint4 *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// A block barrier that orders LDS accesses alone: the wave waits for its own
+// LDS operations, not, as __syncthreads does, for its global stores and copies
+// into LDS still on their way (about a microsecond where a list or scores have
+// just been stored).  What a copy_to_lds brings is not covered.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Copies n 16-byte chunks from global memory straight into LDS (block-wide)
 // with global_load_lds_dwordx4: no registers are held, the copy runs while the
 // block does other work, and it is complete after the block's next
@@ -354,11 +364,13 @@ __device__ __forceinline__ float query_norm(const uint4 *q, int nch) {
 // l+128, ... in order, pair p of a chunk into acc[p]), so a row gives the same
 // bits here as through row_dot.
 // `row(k)` gives the k-th row (k < n) of this wave, or null for an unusable
-// one (its results are reported as not valid); `done(k, valid, dot, nrm)` runs
-// in every lane when row k is complete, in order of k.
-template <int kRows, int kLoads, class RowPtr, class Done>
+// one (its results are reported as not valid); `begin()` runs once the first
+// two pieces are requested (the query's norm is taken there, under their
+// latency); `done(k, valid, dot, nrm)` runs in every lane when row k is
+// complete, in order of k.
+template <int kRows, int kLoads, class RowPtr, class Begin, class Done>
 __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const uint4 *q,
-                                            Done done) {
+                                            Begin begin, Done done) {
     const int lane = lane_id();
     auto has = [&](int u) { return u < kLoads - 1 || u * kWave + lane < nch; };
     constexpr std::integral_constant<int, 0> first{};
@@ -398,6 +410,7 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
         };
         issue(first, 0);
         issue(second, kRows);
+        begin();
         for (int k = 0; k < n; k += 2 * kRows) {
             consume(first, k);
             issue(first, k + 2 * kRows);
@@ -443,6 +456,7 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
             issue(first, 0);
             issue(second, 0);
         }
+        begin();
         for (int k = 0; k < n; ++k) {
             consume(first, k);
             if (k + 1 < n) issue(first, k + 1);

@@ -96,11 +96,12 @@ static void part_ws_layout(DraftArgs &a, void *ws) {
 // kernel); score c goes to scores[b][out0 + c].
 template <int kRows, int kLoads>
 __device__ void draft_score_rows(const DraftArgs &a, int b, int64_t T, bool seq_ok,
-                                 const uint16_t *Hb, const uint4 *q_s, float qq,
-                                 const int32_t *s_cand, int first, int step, int total,
-                                 int64_t out0, uint64_t &best) {
+                                 const uint16_t *Hb, const uint4 *q_s, const int32_t *s_cand,
+                                 int first, int step, int total, int64_t out0, uint64_t &best) {
     const int lane = lane_id();
     const int nch = a.d / 8;
+    float qq = 0.f;
+    if (kLoads == 0 && seq_ok) qq = query_norm(q_s, nch);
     const int n = total > first ? (total - first + step - 1) / step : 0;
     auto row = [&](int k) -> const uint4 * {
         const int32_t j = s_cand[first + k * step];
@@ -119,7 +120,16 @@ __device__ void draft_score_rows(const DraftArgs &a, int b, int64_t T, bool seq_
         if (a.scores && lane == 0) a.scores[(int64_t)b * a.cap + out0 + first + k * step] = s;
     };
     if constexpr (kLoads > 0) {
-        stream_rows<kRows, kLoads>(n, nch, row, q_s, done);
+        // The query's norm under the first loads' latency, unless sixteen waves
+        // have two rows or more each: their loads then fill the CU's path for
+        // longer than the norm takes, and it is ready sooner before them (30
+        // rows of 8 KB in one block: 13.4 against 13.9 us per step; 6 rows:
+        // 14.7 after the loads, 15.0 before).
+        const bool early = step == kFindWavesFused && n > kRows;
+        if (early && seq_ok) qq = query_norm(q_s, nch);
+        stream_rows<kRows, kLoads>(n, nch, row, q_s, [&] {
+            if (!early && seq_ok) qq = query_norm(q_s, nch);
+        }, done);
     } else {
         for (int k = 0; k < n; ++k) {
             const uint4 *r = row(k);
@@ -130,31 +140,29 @@ __device__ void draft_score_rows(const DraftArgs &a, int b, int64_t T, bool seq_
     }
 }
 
-// The block's share of the ranking (Eq. 2 / Eq. 3) over the list s_cand of
-// `total` candidates: list slots w, w + kWaves, ... per wave (hidden), or one
-// slot per group of kGatherLanes lanes (attention).  Returns the block's best key in every thread;
-// `s_q` holds the query row (hidden), `s_key` is kWaves words of LDS.
+// The block's share of the ranking (Eq. 2 / Eq. 3), the entries [lo, hi) of
+// the list s_cand: list slots lo + w, lo + w + kWaves, ... per wave (hidden), or
+// one slot per group of kGatherLanes lanes (attention).  Returns the block's best
+// key in every thread; `s_q` holds the query row (hidden), `s_key` is kWaves
+// words of LDS.
 template <bool kHidden, int kWaves, int kRows, int kLoads>
 __device__ uint64_t rank_candidates(const DraftArgs &a, int b, int64_t T, bool seq_ok,
-                                    const int32_t *s_cand, int total, int64_t out0,
+                                    const int32_t *s_cand, int lo, int hi, int64_t out0,
                                     const uint4 *s_q, uint64_t *s_key) {
     const int w = threadIdx.x / kWave;
     const int lane = lane_id();
     uint64_t best = 0;
     if constexpr (kHidden) {
         const uint16_t *Hb = a.hidden + (int64_t)b * a.hs;
-        const int nch = a.d / 8;
-        const float qq = seq_ok ? query_norm(s_q, nch) : 0.f;
-        draft_score_rows<kRows, kLoads>(a, b, T, seq_ok, Hb, s_q, qq, s_cand, w, kWaves, total,
-                                        out0, best);
-        // (every lane of a wave holds the wave's best)
+        draft_score_rows<kRows, kLoads>(a, b, T, seq_ok, Hb, s_q, s_cand, lo + w, kWaves, hi, out0,
+                                        best);
     } else {
         const float *Ab = a.attn + (int64_t)b * a.as;
         constexpr int kPerPass = kWaves * kWave / kGatherLanes;   // a lane group per candidate
-        for (int c0 = 0; c0 < total; c0 += kPerPass) {
+        for (int c0 = lo; c0 < hi; c0 += kPerPass) {
             const int c = c0 + (int)threadIdx.x / kGatherLanes;
-            const int32_t j = c < total ? s_cand[c] : 0;
-            const bool ok = c < total && seq_ok && j >= 1 && (int64_t)j <= T - 2 &&
+            const int32_t j = c < hi ? s_cand[c] : 0;
+            const bool ok = c < hi && seq_ok && j >= 1 && (int64_t)j <= T - 2 &&
                             (int64_t)(j - 1) < a.n_keys;
             const float g = attn_gather_group(Ab + (ok ? j - 1 : 0), a.ar, a.R,
                                               a.agg == PLD_AGG_SUM, ok);
@@ -163,13 +171,13 @@ __device__ uint64_t rank_candidates(const DraftArgs &a, int b, int64_t T, bool s
                 const uint64_t k = rank_key(s, j);
                 best = k > best ? k : best;
             }
-            if (c < total && a.scores && (threadIdx.x & (kGatherLanes - 1)) == 0)
+            if (c < hi && a.scores && (threadIdx.x & (kGatherLanes - 1)) == 0)
                 a.scores[(int64_t)b * a.cap + out0 + c] = s;
         }
         best = wave_max_u64(best);
     }
     if (lane == 0) s_key[w] = best;
-    __syncthreads();
+    lds_barrier();
     best = 0;
     for (int i = 0; i < kWaves; ++i) best = s_key[i] > best ? s_key[i] : best;
     return best;
@@ -198,7 +206,7 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
     const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
 
     // the token row straight into LDS when it is 16-byte aligned (it does not
-    // wait for the length), then the query row
+    // wait for the length)
     const int64_t T = a.lens[b];
     const bool tok_ok = (T >= 1 && T <= a.tok_stride);   // block-uniform
     const bool seq_ok = kHidden ? (T >= 2 && T - 2 < a.n_rows) : (T >= 2);
@@ -207,27 +215,31 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
                     (int)(a.tok_stride / 4));
     else
         stage_tokens(x, 0, a.tok_stride, s_buf);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    // the query row, which arrives under the search
     if (kHidden && tok_ok && seq_ok)
         copy_to_lds(reinterpret_cast<const uint4 *>(a.hidden + (int64_t)b * a.hs + (T - 2) * a.hr),
                     s_q, a.d / 8);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
 
-    // ---- occurrences (Eq. 1), longest n first, listed in LDS and in cand_pos
+    // ---- occurrences (Eq. 1), longest n first, listed in LDS
     int n_used = -1, total = 0;
-    if (tok_ok) {   // block-uniform
-        n_used = block_search<kWaves, kFindFusedMax / (kWaves * kWave)>(
-            s_buf, T, a.nmin, a.nmax, s_lvl, a.cand_pos + (int64_t)b * a.cap, s_list, total);
-        if (n_used > 0) __syncthreads();   // the list in LDS is complete
-    }
+    if (tok_ok)   // block-uniform
+        n_used = block_search<kWaves, kFindFusedMax / (kWaves * kWave)>(s_buf, T, a.nmin, a.nmax,
+                                                                        s_lvl, s_list, total);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();   // the list and the query row are complete
     if (threadIdx.x == 0) {
         a.cand_count[b] = total;
         a.ngram_used[b] = n_used;
     }
     uint64_t best = 0;
-    if (total > 0)   // block-uniform
-        best = rank_candidates<kHidden, kWaves, kRows, kLoads>(a, b, T, seq_ok, s_list, total, 0, s_q,
-                                                           s_key);
+    if (total > 0) {   // block-uniform
+        best = rank_candidates<kHidden, kWaves, kRows, kLoads>(a, b, T, seq_ok, s_list, 0, total, 0,
+                                                               s_q, s_key);
+        for (int i = (int)threadIdx.x; i < total; i += kWaves * kWave)
+            a.cand_pos[(int64_t)b * a.cap + i] = s_list[i];
+    }
     if (w == 0) write_draft(a, b, T, tok_ok, best, s_buf);
 }
 
@@ -398,9 +410,9 @@ __global__ __launch_bounds__(kWaves * kWave) void draft_part_kernel(DraftArgs a)
     for (int t = 0; t < kPasses; ++t)
         emit_bits(bits[t], lo + (int64_t)t * kPass + (int64_t)threadIdx.x * kLanePos, s_x,
                   out, start[t]);
-    __syncthreads();
+    lds_barrier();
     const uint64_t best =
-        rank_candidates<kHidden, kWaves, kRows, kLoads>(a, b, T, seq_ok, s_x, total, lo, s_q, s_key);
+        rank_candidates<kHidden, kWaves, kRows, kLoads>(a, b, T, seq_ok, s_x, 0, total, lo, s_q, s_key);
     if (threadIdx.x == 0 && best)
         atomicMax((unsigned long long *)&a.keys[(int64_t)b * kKeySlots + (s % kKeySlots)],
                   (unsigned long long)best);

@@ -80,8 +80,7 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void find_fused_kernel(Fin
     }
     int total;
     const int n_used = block_search<kFindWavesFused, G>(s_x, T, a.nmin, a.nmax, s_lvl,
-                                                        a.cand_pos + (int64_t)b * a.cap, nullptr,
-                                                        total);
+                                                        a.cand_pos + (int64_t)b * a.cap, total);
     if (threadIdx.x == 0) {
         a.cand_count[b] = total;
         a.ngram_used[b] = n_used;

@@ -106,19 +106,17 @@ __device__ __forceinline__ uint64_t lane_hits(const int32_t *s, int64_t s0, int6
 
 // ------------------------------------------------------------- block search
 // Writes the positions p0 + l of the set bits l of the wave-uniform mask m to
-// out[run ...] (and out2[run ...] when given) in ascending order; returns run
-// plus the number of bits.  The mask becomes the execution mask of the
+// out[run ...] (global memory or LDS) in ascending order; returns run plus the
+// number of bits.  The mask becomes the execution mask of the
 // stores; an entry's byte offset fits in 32 bits (fewer than 2^30 positions
 // per row).
-__device__ __forceinline__ int emit_group(uint64_t m, int p0, int32_t *out, int32_t *out2,
-                                          int run) {
+__device__ __forceinline__ int emit_group(uint64_t m, int p0, int32_t *out, int run) {
     if (__builtin_amdgcn_inverse_ballot_w64(m)) {
         const uint32_t below = __builtin_amdgcn_mbcnt_hi(
             (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
         const uint32_t off = ((uint32_t)run + below) << 2;
         const int32_t p = p0 + lane_id();
         *reinterpret_cast<int32_t *>(reinterpret_cast<char *>(out) + off) = p;
-        if (out2) *reinterpret_cast<int32_t *>(reinterpret_cast<char *>(out2) + off) = p;
     }
     return run + (int)__popcll(m);
 }
@@ -134,12 +132,11 @@ __device__ __forceinline__ int emit_group(uint64_t m, int p0, int32_t *out, int3
 // of a level at once, while any bit is left.  On the single CU that searches
 // a sequence the pass costs a few instructions per 64 positions and level.  Returns n (0: no occurrence)
 // and the count; with n > 0 the occurrences are written in ascending order
-// to out (and out2 when given).  s_lvl: kW x kMaxNgram ints of LDS.  Call
+// to out (global memory or LDS).  s_lvl: kW x kMaxNgram ints of LDS.  Call
 // with T in [1, kW * G * 64], from the whole block.
 template <int kW, int G>
 __device__ __forceinline__ int block_search(const int32_t *s_x, int64_t T, int nmin, int nmax,
-                                            int (*s_lvl)[kMaxNgram], int32_t *out, int32_t *out2,
-                                            int &total) {
+                                            int (*s_lvl)[kMaxNgram], int32_t *out, int &total) {
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int lane = lane_id();
     const int w0 = w * G * kWave;
@@ -204,7 +201,7 @@ __device__ __forceinline__ int block_search(const int32_t *s_x, int64_t T, int n
             });
         }
     }
-    __syncthreads();
+    lds_barrier();
     // the longest n with an occurrence, and this wave's offset in the list:
     // lane i < kW holds wave i's count of the level
     int n_used = 0, run = 0;
@@ -223,7 +220,7 @@ __device__ __forceinline__ int block_search(const int32_t *s_x, int64_t T, int n
     if (n_used > 0 && some) {   // uniform; ascending: wave, then group, then lane
         if (n_used > 1) levels(m0, n_used - 1, [](int, int) {});
 #pragma unroll
-        for (int i = 0; i < G; ++i) run = emit_group(m0[i], w0 + i * kWave, out, out2, run);
+        for (int i = 0; i < G; ++i) run = emit_group(m0[i], w0 + i * kWave, out, run);
     }
     return n_used;
 }

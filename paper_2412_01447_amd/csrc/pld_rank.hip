@@ -236,11 +236,13 @@ __global__ __launch_bounds__(256) void select_draft_kernel(SelectDraftArgs a) {
 // best key.
 template <int kRows, int kLoads, int kW>
 __device__ void score_rows(const RankHiddenArgs &a, int b, int64_t T, bool seq_ok,
-                           const uint16_t *Hb, const uint4 *q_s, float qq, uint32_t first,
-                           uint32_t end, uint32_t seq_start, int32_t jv0, uint64_t &best) {
+                           const uint16_t *Hb, const uint4 *q_s, uint32_t first, uint32_t end,
+                           uint32_t seq_start, int32_t jv0, uint64_t &best) {
     const RankCommon &c = a.c;
     const int lane = lane_id();
     const int nch = a.d / 8;
+    float qq = 0.f;
+    if (kLoads == 0 && seq_ok) qq = query_norm(q_s, nch);
     const uint32_t n = end > first ? (end - first + kW - 1) / kW : 0;
     for (uint32_t base = 0; base < n; base += kWave) {
         const uint32_t nb = min((uint32_t)kWave, n - base);
@@ -266,7 +268,9 @@ __device__ void score_rows(const RankHiddenArgs &a, int b, int64_t T, bool seq_o
                 c.scores[(int64_t)b * c.cap + (first + (base + k) * kW - seq_start)] = s;
         };
         if constexpr (kLoads > 0) {
-            stream_rows<kRows, kLoads>((int)nb, nch, row, q_s, done);
+            stream_rows<kRows, kLoads>((int)nb, nch, row, q_s, [&] {
+                if (base == 0 && seq_ok) qq = query_norm(q_s, nch);
+            }, done);
         } else {
             for (int k = 0; k < (int)nb; ++k) {
                 const uint4 *r = row(k);
@@ -311,12 +315,10 @@ __device__ void hidden_block(const RankHiddenArgs &a, uint32_t k, uint32_t g, ui
         if (seq_ok) copy_to_lds(reinterpret_cast<const uint4 *>(Hb + (T - 2) * a.hr), q_s, nch);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        const float qq = seq_ok ? query_norm(q_s, nch) : 0.f;
         uint64_t best = 0;
-        score_rows<kRows, kLoads, kW>(a, b, T, seq_ok, Hb, q_s, qq, first, seg_hi, pre[b], jv0,
-                                      best);
+        score_rows<kRows, kLoads, kW>(a, b, T, seq_ok, Hb, q_s, first, seg_hi, pre[b], jv0, best);
         if (lane == 0) s_best[w] = best;
-        __syncthreads();                                       // also: q_s is restaged next
+        lds_barrier();                                         // also: q_s is restaged next
         if (threadIdx.x == 0) {
             uint64_t m = s_best[0];
             for (int i = 1; i < kW; ++i) m = s_best[i] > m ? s_best[i] : m;
