@@ -480,12 +480,15 @@ int pld_accept_commit(const int32_t *draft, const int32_t *draft_len, int B, int
  *                     launch compacts the lists and writes the selection and
  *                     the draft (with ngram_min < ngram_max a counting launch
  *                     comes first).  Spreads long contexts and long lists
- *                     over S x B blocks.
+ *                     over S x B blocks.  With tok_stride <= 8192, a batch
+ *                     whose S blocks per sequence roughly fit on the GPU
+ *                     together takes one launch instead, up to S blocks
+ *                     sharing a sequence's occurrences.
  *   workspace       S > 1: at least pld_draft_workspace_bytes(B, S) bytes of
  *                   its own (not shared with the ranking or verification
  *                   calls), zero before the first call.  Its first B*128
  *                   bytes (the key slots) are left zero by every call; the
- *                   rest is per-block counts, rewritten by each call.  Calls
+ *                   rest is per-block counts, rewritten by calls that use them.  Calls
  *                   that share one workspace must not overlap in time.
  *   cand_pos, scores  entries past cand_count are unspecified on return.
  *   scores          may be NULL.

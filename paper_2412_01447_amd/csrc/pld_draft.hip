@@ -3,12 +3,13 @@
 // hidden-state cosine (Eq. 2) or aggregated attention (Eq. 3, Sec. 7.1),
 // selection of the best occurrence, and the draft span (Sec. 4.3).
 //
-// S == 1 (tok_stride <= 8192): one 1024-thread block owns a sequence.  It
+// tok_stride <= 8192, S == 1 or a team of up to S blocks: a 1024-thread block
 //   copies the token row and the query row into LDS, finds the occurrences
-//   (the one-block search of the find call, listing them in LDS as well),
-//   scores them with the same per-row routines as the separate ranking calls
-//   (bit-identical scores), selects, and writes the draft -- one launch.
-// S  > 1: the positions are partitioned.  Block s of a sequence owns the
+//   (the one-block search of the find call, listing them in LDS), scores its
+//   share of them with the same per-row routines as the separate ranking calls
+//   (bit-identical scores), and the block that finishes last selects and writes
+//   the draft -- one launch.
+// otherwise, S > 1: the positions are partitioned.  Block s of a sequence owns the
 //   positions [s*P, (s+1)*P) (P <= 8192, a multiple of 8): it stages only
 //   those tokens, finds its own occurrences, scores them, and folds its best
 //   key into the sequence's key slots.  Its part of the occurrence list (and
@@ -192,16 +193,41 @@ __device__ void write_draft(const DraftArgs &a, int b, int64_t T, bool tok_ok, u
                        a.draft + (int64_t)b * a.K, a.draft_len + b);
 }
 
-// ------------------------------------------------------------------- S == 1
+// ------------------------------------------------- rows of up to 8192 tokens
+// A team of blocks per sequence: each searches the whole row (from L2 after the
+// first; the search of 8192 tokens takes a block about a microsecond), so each
+// knows the list and its share of it, no list is compacted, and the block that
+// finishes last writes the choice: one launch where the split form takes two,
+// three with a range of n-gram lengths.  What bounds a block is its CU's load path
+// and issue slots (30 rows of 8 KB: 1.6 us to request, 0.6 us per row and wave to
+// reduce), so few rows per block pay for handing the keys over (about 1.5 us).
+// Rows per block (us per step, 16 | 8 | 4 rows): 8 x 4096 tokens, 50 occurrences,
+// d = 4096 13.6 | 13.1 | 12.7, 10 x 4096, 100, d = 1024 18.6 | 14.5 | 15.3, 2 x 2048,
+// 30, d = 8192 13.9 | 13.2 | 12.7, 1 x 8192, 800, d = 4096 13.9 | 13.9 | 14.6 (the
+// split form: 17.0, 18.4, 15.9, 17.2); scored by one block up to 64 KB, against
+// 128 KB: the same or faster.  Attention: 16 to 64 candidates per block within 2%.
+constexpr int kTeamMax = 128;             // blocks per sequence
+constexpr int kTeamBytes = 65536;         // hidden: rows' bytes per block, 4 to 8 rows
+constexpr int kAloneGathers = 256, kTeamGathers = 32;   // attention: candidates
+// Blocks of a team of `most` that share the scoring of `total` candidates.
+template <bool kHidden>
+__device__ __forceinline__ int team_size(const DraftArgs &a, int total, int most) {
+    if (most == 1) return 1;
+    if (kHidden ? (int64_t)total * a.d * 2 <= kTeamBytes : total <= kAloneGathers) return 1;
+    const int share = kHidden ? max(4, min(8, kTeamBytes / (2 * a.d))) : kTeamGathers;
+    return min(most, (total + share - 1) / share);
+}
+
 template <bool kHidden, int kRows, int kLoads>
 __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArgs a) {
     constexpr int kWaves = kFindWavesFused;
+    constexpr int kThreads = kWaves * kWave;
     __shared__ __align__(16) int32_t s_buf[kFindFusedMax];   // the tokens
     __shared__ int32_t s_list[kFindFusedMax];                // the occurrence list
     extern __shared__ uint4 s_q[];                           // query row H[T-2] (hidden)
     __shared__ int s_lvl[kWaves][kMaxNgram];
     __shared__ uint64_t s_key[kWaves];
-    const int b = blockIdx.y;
+    const int part = blockIdx.x, b = blockIdx.y;
     const int w = threadIdx.x / kWave;
     const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
 
@@ -229,18 +255,50 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
                                                                         s_lvl, s_list, total);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();   // the list and the query row are complete
-    if (threadIdx.x == 0) {
+    if (part == 0 && threadIdx.x == 0) {
         a.cand_count[b] = total;
         a.ngram_used[b] = n_used;
     }
+    const int team = team_size<kHidden>(a, total, (int)gridDim.x);
+    if (part >= team) return;   // block-uniform
     uint64_t best = 0;
     if (total > 0) {   // block-uniform
-        best = rank_candidates<kHidden, kWaves, kRows, kLoads>(a, b, T, seq_ok, s_list, 0, total, 0,
+        int lo = 0, hi = total;
+        if (team > 1) {   // equal contiguous shares
+            const int q = total / team, r = total % team;
+            lo = part * q + min(part, r);
+            hi = lo + q + (part < r ? 1 : 0);
+        }
+        best = rank_candidates<kHidden, kWaves, kRows, kLoads>(a, b, T, seq_ok, s_list, lo, hi, 0,
                                                                s_q, s_key);
-        for (int i = (int)threadIdx.x; i < total; i += kWaves * kWave)
+        for (int i = lo + (int)threadIdx.x; i < hi; i += kThreads)
             a.cand_pos[(int64_t)b * a.cap + i] = s_list[i];
     }
-    if (w == 0) write_draft(a, b, T, tok_ok, best, s_buf);
+    if (w != 0) return;
+    if (team > 1) {
+        // The last block of the team to fold its key writes the choice: the
+        // key goes to the sequence's first slot by an atomic maximum whose
+        // return is waited for, then the block counts itself done in the
+        // second slot, and the one that completes the count takes the key back
+        // and returns both slots to zero.  Atomics alone carry the key, so no
+        // cache is written back or invalidated.
+        unsigned long long *slot = (unsigned long long *)(a.keys + (int64_t)b * kKeySlots);
+        int last = 0;
+        if (threadIdx.x == 0) {
+            const unsigned long long prev = atomicMax(slot, (unsigned long long)best);
+            asm volatile("" ::"v"(prev));   // the returned value must arrive here
+            __builtin_amdgcn_s_waitcnt(0);
+            last = atomicAdd(slot + 1, 1ull) == (unsigned long long)(team - 1);
+            if (last) {
+                best = atomicExch(slot, 0ull);
+                atomicExch(slot + 1, 0ull);
+            }
+        }
+        if (!__builtin_amdgcn_readfirstlane(last)) return;
+        best = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(best >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
+    }
+    write_draft(a, b, T, tok_ok, best, s_buf);
 }
 
 // ------------------------------------------------------------------- S  > 1
@@ -651,8 +709,26 @@ static DraftArgs make_draft(const int32_t *tokens, int64_t tok_stride, const int
 template <bool kHidden, int kRows, int kLoads>
 static void launch_draft_as(const DraftArgs &a, hipStream_t s) {
     const size_t lds = kHidden ? (size_t)(a.d / 8) * sizeof(uint4) : 0;
-    if (a.S == 1) {
-        hipLaunchKernelGGL((draft_kernel<kHidden, kRows, kLoads>), dim3(1, a.B),
+    // Rows of up to 8192 tokens: one block per sequence, or a team of as many as
+    // asked for and fit on the GPU together, unless a sequence's share of the GPU
+    // is so much less than the blocks asked for that the slices of the split form,
+    // four blocks per CU, balance the batch's lists better.  Measured (us per
+    // step, team | split; S asked for, `fit` blocks per sequence resident):
+    // hidden, 16 x 8192 (S 34, fit 16) 25.9 | 28.7, 24 x 8192 (S 37, fit 10) 35.8 |
+    // 32.0; attention, 12 x 3000 (S 28, fit 21) 12.8 | 16.4, 16 x 8192 (S 34, fit 16)
+    // 19.7 | 18.8, 32 x 8192 (S 40, fit 8) 30.1 | 27.7.
+    int team = a.S == 1 ? 1 : 0;
+    if (a.S > 1 && a.tok_stride <= kFindFusedMax) {
+        const int fit = resident_blocks(
+            reinterpret_cast<const void *>(&draft_kernel<kHidden, kRows, kLoads>),
+            kFindWavesFused * kWave, lds) / a.B;
+        if (2 * a.S <= (kHidden ? 5 : 3) * fit) {
+            team = a.S < fit ? a.S : fit;
+            if (team > kTeamMax) team = kTeamMax;
+        }
+    }
+    if (team > 0) {
+        hipLaunchKernelGGL((draft_kernel<kHidden, kRows, kLoads>), dim3(team, a.B),
                            dim3(kFindWavesFused * kWave), lds, s, a);
         return;
     }

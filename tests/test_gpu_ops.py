@@ -999,6 +999,68 @@ def test_draft_finish_read_ahead_limits(split):
     test_draft_fused_parity((2, 4096, 1, 1, 1, 64, 0, 6, 13), split)
 
 
+@pytest.mark.parametrize("split", [192, 240, 241, 1000])
+def test_draft_finish_limits_past_the_team(split):
+    """The same limits where no team takes the call: 15360 positions, every one an
+    occurrence, in 240 parts of 64 (the read-ahead exactly), 192 of 80, 241 of 64
+    (more parts than it covers) and 1000 of 16."""
+    test_draft_fused_parity((2, 15360, 1, 1, 1, 64, 0, 6, 14), split)
+
+
+@pytest.mark.parametrize("d,R,total", [(512, 0, 64), (512, 0, 65), (512, 0, 1000), (4096, 0, 8),
+                                       (4096, 0, 9), (4096, 0, 45), (8192, 0, 5), (9000, 0, 23),
+                                       (64, 0, 3000), (0, 5, 256), (0, 5, 257), (0, 70, 1000),
+                                       (0, 3, 4094)])
+def test_draft_team(d, R, total):
+    """A team of blocks drafting one sequence: lists at the sizes where a block stops
+    scoring alone (64 KB of rows, 256 attention candidates), with shares of
+    unequal length, more blocks asked for than have a share, an empty list, one
+    longer than the others, an invalid length, no eligible candidate, n-gram
+    ranges; two calls in turn on one workspace; the same bits as the separate
+    calls."""
+    say("draft team", d, R, total)
+    B, T, K = 4, 4096, 6
+    rng = np.random.default_rng(d + R + total)
+    toks = rng.integers(1, 1 << 20, size=(B, T)).astype(np.int32)
+    lens = np.array([T, T, T - 1, T + 1], np.int32)
+    for b, n in ((0, total), (2, min(total, 11))):
+        toks[b, 1 + rng.choice(lens[b] - 2, n, replace=False)] = 0
+        toks[b, lens[b] - 1] = 0
+    i32 = dict(dtype=torch.int32, device="cuda")
+    td, ld = d_i32(toks), d_i32(lens)
+    if d:
+        art = d_bf16(synth.f32_to_bf16_bits(rng.standard_normal((B, T, d)).astype(np.float32)))
+    else:
+        art = d_f32(rng.random((B, R, T), dtype=np.float32))
+    for nmin, nmax in ((1, 1), (1, 3)):
+        cp, cc, nu = oracle.find(toks, lens, nmin, nmax)
+        assert cc[0] == total and cc[1] == 0 and cc[3] == 0 or nmax > 1
+        for S in (2, 3, 7, 64, 160):
+            ws = draft_workspace(B, S)
+            for th in (-math.inf, 1e9):
+                o = [torch.full((B, T), -1, **i32), torch.zeros(B, **i32), torch.zeros(B, **i32),
+                     torch.zeros(B, **i32), torch.zeros(B, dtype=torch.float32, device="cuda"),
+                     torch.zeros((B, K), **i32), torch.zeros(B, **i32)]
+                sc = torch.zeros((B, T), dtype=torch.float32, device="cuda")
+                call, ref = ((pld.pld_draft_hidden, gpu_rank_hidden) if d else
+                             (pld.pld_draft_attn, lambda *x, **k: gpu_rank_attn(
+                                 *x, pld.PLD_AGG_SUM, **k)))
+                call(td, ld, nmin, nmax, art, K, *o, threshold=th, scores=sc, blocks_per_seq=S,
+                     workspace=ws)
+                rsc, rbp, rbs = ref(art, lens, cp, cc, threshold=th)
+                torch.cuda.synchronize()
+                g = [t.cpu().numpy() for t in o]
+                what = f"n{nmin}-{nmax} S{S} th{th}"
+                check_find((g[0], g[1], g[2]), (cp, cc, nu), what)
+                gs = sc.cpu().numpy()
+                for b in range(B):
+                    assert np.array_equal(gs[b, :cc[b]], rsc[b, :cc[b]]), what
+                assert np.array_equal(g[3], rbp) and np.array_equal(g[4], rbs), what
+                rd, rl = oracle.emit(toks, lens, rbp, K)
+                assert np.array_equal(g[5], rd) and np.array_equal(g[6], rl), what
+                assert draft_keys_zero(ws, B), what
+
+
 def test_autotune_split_keeps_the_results():
     """DraftStep.autotune_split times a few blocks-per-sequence choices (8-wave
     blocks for small grids, 4-wave blocks for large ones) and keeps one; the
