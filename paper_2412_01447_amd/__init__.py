@@ -116,29 +116,43 @@ def _load():
     return _lib
 
 
+# Marshalling is on the path of every unprepared call (the generation loop issues
+# two to seven a step), so it stays short: pointers and the stream travel as plain
+# integers, a tensor's strides are read once, library functions are looked up once.
+_torch = None
+
+
+def _th():
+    """torch, imported on first use (building the library does not need it)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
-        import torch
+        torch = _torch or _th()
+        if torch.cuda.is_initialized():   # what current_stream() wraps in an object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _need(t, dtype, name, dims):
+    """Checks a device tensor of `dims` dimensions, the last contiguous; its strides."""
     if t.dtype != dtype or t.dim() != dims or not t.is_cuda:
         raise TypeError(f"{name}: expected a {dims}-d {dtype} device tensor, got "
                         f"{tuple(t.shape)} {t.dtype} on {t.device}")
-    if t.stride(-1) != 1:
+    st = t.stride()
+    if st[-1] != 1:
         raise TypeError(f"{name}: the last dimension must be contiguous")
-
-
-def _call(name, *args):
-    rc = getattr(_load(), name)(*args)
-    if rc != PLD_OK:
-        raise PLDError(name, rc)
+    return st
 
 
 class Prepared:
@@ -149,11 +163,10 @@ class Prepared:
 
     def __init__(self, name, args):
         self.name = name
-        self.fn = getattr(_load(), name)
-        conv = []
-        for a, t in zip(args, self.fn.argtypes):
-            conv.append(a if isinstance(a, (ctypes.c_void_p,)) or a is None else t(a))
-        self.args = tuple(conv)
+        # converted once, to the declared types; a function object of its own, without
+        # argument types, passes them on as they are
+        self.args = tuple(a if a is None else t(a) for a, t in zip(args, _SIGNATURES[name][0]))
+        self.fn = _load()[name]
 
     def __call__(self):
         rc = self.fn(*self.args)
@@ -164,7 +177,9 @@ class Prepared:
 def _run(name, args, prepare):
     if prepare:
         return Prepared(name, args)
-    _call(name, *args)
+    rc = getattr(_lib or _load(), name)(*args)
+    if rc != PLD_OK:
+        raise PLDError(name, rc)
 
 
 def pld_version():
@@ -192,30 +207,30 @@ def pld_find_scratch_bytes(B, tok_stride):
 
 
 def _nbytes(t):
-    return 0 if t is None else t.numel() * t.element_size()
+    return 0 if t is None else t.nbytes
 
 
 def pld_find_candidates(tokens, lens, ngram_min, ngram_max, cand_pos, cand_count, ngram_used,
                         scratch=None, stream=None, prepare=False):
     """tokens int32 [B][tok_stride]; writes cand_pos [B][cap], cand_count [B], ngram_used [B]."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     B = tokens.shape[0]
-    return _run("pld_find_candidates", (_ptr(tokens), tokens.stride(0), _ptr(lens), B, ngram_min,
-          ngram_max, _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), _ptr(ngram_used),
+    return _run("pld_find_candidates", (_ptr(tokens), ts[0], _ptr(lens), B, ngram_min,
+          ngram_max, _ptr(cand_pos), cs[0], _ptr(cand_count), _ptr(ngram_used),
           _ptr(scratch), _nbytes(scratch), _stream(stream),), prepare)
 
 
 def pld_rank_hidden(hidden, lens, cand_pos, cand_count, best_pos, best_score, workspace,
                     threshold=float("-inf"), scores=None, stream=None, prepare=False):
     """hidden bf16 [B][n_rows][d]; writes best_pos [B], best_score [B] and optionally scores."""
-    import torch
-    _need(hidden, torch.bfloat16, "hidden", 3)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    hs = _need(hidden, torch.bfloat16, "hidden", 3)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     B, n_rows, d = hidden.shape
-    return _run("pld_rank_hidden", (_ptr(hidden), hidden.stride(0), hidden.stride(1), n_rows, d,
-          _ptr(lens), _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), B, float(threshold),
+    return _run("pld_rank_hidden", (_ptr(hidden), hs[0], hs[1], n_rows, d,
+          _ptr(lens), _ptr(cand_pos), cs[0], _ptr(cand_count), B, float(threshold),
           _ptr(scores), _ptr(best_pos), _ptr(best_score), _ptr(workspace),
           _nbytes(workspace), _stream(stream),), prepare)
 
@@ -223,34 +238,34 @@ def pld_rank_hidden(hidden, lens, cand_pos, cand_count, best_pos, best_score, wo
 def pld_rank_attn(attn, lens, cand_pos, cand_count, best_pos, best_score, workspace,
                   agg=PLD_AGG_SUM, threshold=float("-inf"), scores=None, stream=None, prepare=False):
     """attn fp32 [B][R][n_keys] (query row T-2 per selected head); agg SUM or MAX."""
-    import torch
-    _need(attn, torch.float32, "attn", 3)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    as_ = _need(attn, torch.float32, "attn", 3)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     B, R, n_keys = attn.shape
-    return _run("pld_rank_attn", (_ptr(attn), attn.stride(0), attn.stride(1), n_keys, R, int(agg),
-          _ptr(lens), _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), B, float(threshold),
+    return _run("pld_rank_attn", (_ptr(attn), as_[0], as_[1], n_keys, R, int(agg),
+          _ptr(lens), _ptr(cand_pos), cs[0], _ptr(cand_count), B, float(threshold),
           _ptr(scores), _ptr(best_pos), _ptr(best_score), _ptr(workspace),
           _nbytes(workspace), _stream(stream),), prepare)
 
 
 def pld_emit_draft(tokens, lens, best_pos, K, draft, draft_len, stream=None, prepare=False):
     """Writes draft [B][K] (padded with -1) and draft_len [B]."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
     _need(draft, torch.int32, "draft", 2)
     if draft.shape[1] != K or draft.stride(0) != K:
         raise TypeError("draft must be a contiguous [B][K] tensor")
-    return _run("pld_emit_draft", (_ptr(tokens), tokens.stride(0), _ptr(lens), _ptr(best_pos),
+    return _run("pld_emit_draft", (_ptr(tokens), ts[0], _ptr(lens), _ptr(best_pos),
           tokens.shape[0], K, _ptr(draft), _ptr(draft_len), _stream(stream),), prepare)
 
 
 def pld_verify_greedy(logits, draft, draft_len, accept_len, out_tokens, out_count, workspace,
                       stream=None, prepare=False):
     """logits fp32 or bf16 [B][K+1][V]; writes accept_len [B], out_tokens [B][K+1], out_count [B]."""
-    import torch
+    torch = _torch or _th()
     if logits.dtype not in (torch.float32, torch.bfloat16):
         raise TypeError("logits must be float32 or bfloat16")
-    _need(logits, logits.dtype, "logits", 3)
+    ls = _need(logits, logits.dtype, "logits", 3)
     B, K1, V = logits.shape
     K = K1 - 1
     if draft.shape != (B, K) or draft.stride(0) != K:
@@ -258,7 +273,7 @@ def pld_verify_greedy(logits, draft, draft_len, accept_len, out_tokens, out_coun
     if out_tokens.shape != (B, K1) or out_tokens.stride(0) != K1:
         raise TypeError("out_tokens must be a contiguous [B][K+1] tensor")
     dtype = PLD_F32 if logits.dtype == torch.float32 else PLD_BF16
-    return _run("pld_verify_greedy", (_ptr(logits), dtype, logits.stride(0), logits.stride(1), V, K,
+    return _run("pld_verify_greedy", (_ptr(logits), dtype, ls[0], ls[1], V, K,
           _ptr(draft), _ptr(draft_len), B, _ptr(accept_len), _ptr(out_tokens), _ptr(out_count),
           _ptr(workspace), _nbytes(workspace), _stream(stream),), prepare)
 
@@ -267,10 +282,10 @@ def pld_verify_greedy_noalloc(logits, draft, draft_len, accept_len, out_tokens, 
                               stream=None, prepare=False):
     """pld_verify_greedy without a workspace: the row maxima live in the library's static
     per-GPU array (B*(K+1) <= NOALLOC_MAX_KEYS); calls on one GPU must not overlap."""
-    import torch
+    torch = _torch or _th()
     if logits.dtype not in (torch.float32, torch.bfloat16):
         raise TypeError("logits must be float32 or bfloat16")
-    _need(logits, logits.dtype, "logits", 3)
+    ls = _need(logits, logits.dtype, "logits", 3)
     B, K1, V = logits.shape
     K = K1 - 1
     if draft.shape != (B, K) or draft.stride(0) != K:
@@ -278,8 +293,8 @@ def pld_verify_greedy_noalloc(logits, draft, draft_len, accept_len, out_tokens, 
     if out_tokens.shape != (B, K1) or out_tokens.stride(0) != K1:
         raise TypeError("out_tokens must be a contiguous [B][K+1] tensor")
     dtype = PLD_F32 if logits.dtype == torch.float32 else PLD_BF16
-    return _run("pld_verify_greedy_noalloc", (_ptr(logits), dtype, logits.stride(0),
-          logits.stride(1), V, K, _ptr(draft), _ptr(draft_len), B, _ptr(accept_len),
+    return _run("pld_verify_greedy_noalloc", (_ptr(logits), dtype, ls[0],
+          ls[1], V, K, _ptr(draft), _ptr(draft_len), B, _ptr(accept_len),
           _ptr(out_tokens), _ptr(out_count), _stream(stream),), prepare)
 
 
@@ -298,11 +313,11 @@ def pld_select_prefix(tokens, lens, cand_pos, cand_count, best_pos, best_score, 
                       scores=None, stream=None, prepare=False):
     """Prompt lookup's selection over the occurrence lists: longest matching prefix (up to
     max_match tokens), earliest among equals; writes best_pos [B], best_score [B]."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
-    return _run("pld_select_prefix", (_ptr(tokens), tokens.stride(0), _ptr(lens), _ptr(cand_pos),
-          cand_pos.stride(0), _ptr(cand_count), tokens.shape[0], int(max_match), _ptr(scores),
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
+    return _run("pld_select_prefix", (_ptr(tokens), ts[0], _ptr(lens), _ptr(cand_pos),
+          cs[0], _ptr(cand_count), tokens.shape[0], int(max_match), _ptr(scores),
           _ptr(best_pos), _ptr(best_score), _stream(stream),), prepare)
 
 
@@ -310,15 +325,15 @@ def pld_commit(tokens, lens, out_tokens, out_count, limit=None, stats=None, stre
                prepare=False):
     """Appends out_tokens[b][:out_count[b]] to tokens[b] (up to limit[b]), advances lens and
     adds (emitted, steps) to stats [B][2] int64 when given."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
     B, K1 = out_tokens.shape
     if out_tokens.stride(0) != K1:
         raise TypeError("out_tokens must be a contiguous [B][K+1] tensor")
     if stats is not None and (stats.dtype != torch.int64 or tuple(stats.shape) != (B, 2)
                               or not stats.is_contiguous()):
         raise TypeError("stats must be a contiguous int64 [B][2] tensor")
-    return _run("pld_commit", (_ptr(tokens), tokens.stride(0), _ptr(lens), _ptr(limit),
+    return _run("pld_commit", (_ptr(tokens), ts[0], _ptr(lens), _ptr(limit),
           _ptr(out_tokens), _ptr(out_count), B, K1 - 1, _ptr(stats), _stream(stream),), prepare)
 
 
@@ -327,8 +342,8 @@ def pld_accept_commit(draft, draft_len, accept_len, out_tokens, out_count, token
     """pld_verify_accept then pld_commit in one launch: the accepted length and emitted
     tokens from the row maxima in the workspace, appended to tokens[b] (up to limit[b]),
     lens advanced, (emitted, steps) added to stats [B][2] int64 when given."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
     B, K = draft.shape
     if draft.stride(0) != K or out_tokens.shape != (B, K + 1) or out_tokens.stride(0) != K + 1:
         raise TypeError("draft [B][K] and out_tokens [B][K+1] must be contiguous")
@@ -337,7 +352,7 @@ def pld_accept_commit(draft, draft_len, accept_len, out_tokens, out_count, token
         raise TypeError("stats must be a contiguous int64 [B][2] tensor")
     return _run("pld_accept_commit", (
         _ptr(draft), _ptr(draft_len), B, K, _ptr(accept_len), _ptr(out_tokens), _ptr(out_count),
-        _ptr(tokens), tokens.stride(0), _ptr(lens), _ptr(limit), _ptr(stats), _ptr(workspace),
+        _ptr(tokens), ts[0], _ptr(lens), _ptr(limit), _ptr(stats), _ptr(workspace),
         _nbytes(workspace), _stream(stream),), prepare)
 
 
@@ -346,17 +361,17 @@ def pld_draft_hidden(tokens, lens, ngram_min, ngram_max, hidden, K, cand_pos, ca
                      scores=None, blocks_per_seq=1, workspace=None, stream=None, prepare=False):
     """find + hidden-state ranking + emit in one call (blocks_per_seq 1: tok_stride <= 8192;
     more: a workspace of pld_draft_workspace_bytes(B, blocks_per_seq) bytes)."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
-    _need(hidden, torch.bfloat16, "hidden", 3)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
+    hs = _need(hidden, torch.bfloat16, "hidden", 3)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     if draft.shape[1] != K or draft.stride(0) != K:
         raise TypeError("draft must be a contiguous [B][K] tensor")
     B, n_rows, d = hidden.shape
     return _run("pld_draft_hidden", (
-        _ptr(tokens), tokens.stride(0), _ptr(lens), tokens.shape[0], ngram_min, ngram_max,
-        _ptr(hidden), hidden.stride(0), hidden.stride(1), n_rows, d, float(threshold), K,
-        _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), _ptr(ngram_used), _ptr(scores),
+        _ptr(tokens), ts[0], _ptr(lens), tokens.shape[0], ngram_min, ngram_max,
+        _ptr(hidden), hs[0], hs[1], n_rows, d, float(threshold), K,
+        _ptr(cand_pos), cs[0], _ptr(cand_count), _ptr(ngram_used), _ptr(scores),
         _ptr(best_pos), _ptr(best_score), _ptr(draft), _ptr(draft_len), int(blocks_per_seq),
         _ptr(workspace), _nbytes(workspace), _stream(stream)), prepare)
 
@@ -367,17 +382,17 @@ def pld_draft_attn(tokens, lens, ngram_min, ngram_max, attn, K, cand_pos, cand_c
                    stream=None, prepare=False):
     """find + attention ranking + emit in one call (blocks_per_seq 1: tok_stride <= 8192;
     more: a workspace of pld_draft_workspace_bytes(B, blocks_per_seq) bytes)."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
-    _need(attn, torch.float32, "attn", 3)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
+    as_ = _need(attn, torch.float32, "attn", 3)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     if draft.shape[1] != K or draft.stride(0) != K:
         raise TypeError("draft must be a contiguous [B][K] tensor")
     B, R, n_keys = attn.shape
     return _run("pld_draft_attn", (
-        _ptr(tokens), tokens.stride(0), _ptr(lens), tokens.shape[0], ngram_min, ngram_max,
-        _ptr(attn), attn.stride(0), attn.stride(1), n_keys, R, int(agg), float(threshold), K,
-        _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), _ptr(ngram_used), _ptr(scores),
+        _ptr(tokens), ts[0], _ptr(lens), tokens.shape[0], ngram_min, ngram_max,
+        _ptr(attn), as_[0], as_[1], n_keys, R, int(agg), float(threshold), K,
+        _ptr(cand_pos), cs[0], _ptr(cand_count), _ptr(ngram_used), _ptr(scores),
         _ptr(best_pos), _ptr(best_score), _ptr(draft), _ptr(draft_len), int(blocks_per_seq),
         _ptr(workspace), _nbytes(workspace), _stream(stream)), prepare)
 
@@ -385,24 +400,24 @@ def pld_draft_attn(tokens, lens, ngram_min, ngram_max, attn, K, cand_pos, cand_c
 def pld_score_hidden(hidden, lens, cand_pos, cand_count, workspace, threshold=float("-inf"),
                      scores=None, stream=None, prepare=False):
     """Scoring half of pld_rank_hidden: per-sequence best keys into the workspace."""
-    import torch
-    _need(hidden, torch.bfloat16, "hidden", 3)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    hs = _need(hidden, torch.bfloat16, "hidden", 3)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     B, n_rows, d = hidden.shape
-    return _run("pld_score_hidden", (_ptr(hidden), hidden.stride(0), hidden.stride(1), n_rows, d,
-          _ptr(lens), _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), B, float(threshold),
+    return _run("pld_score_hidden", (_ptr(hidden), hs[0], hs[1], n_rows, d,
+          _ptr(lens), _ptr(cand_pos), cs[0], _ptr(cand_count), B, float(threshold),
           _ptr(scores), _ptr(workspace), _nbytes(workspace), _stream(stream),), prepare)
 
 
 def pld_score_attn(attn, lens, cand_pos, cand_count, workspace, agg=PLD_AGG_SUM,
                    threshold=float("-inf"), scores=None, stream=None, prepare=False):
     """Scoring half of pld_rank_attn."""
-    import torch
-    _need(attn, torch.float32, "attn", 3)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    as_ = _need(attn, torch.float32, "attn", 3)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     B, R, n_keys = attn.shape
-    return _run("pld_score_attn", (_ptr(attn), attn.stride(0), attn.stride(1), n_keys, R, int(agg),
-          _ptr(lens), _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), B, float(threshold),
+    return _run("pld_score_attn", (_ptr(attn), as_[0], as_[1], n_keys, R, int(agg),
+          _ptr(lens), _ptr(cand_pos), cs[0], _ptr(cand_count), B, float(threshold),
           _ptr(scores), _ptr(workspace), _nbytes(workspace), _stream(stream),), prepare)
 
 
@@ -410,16 +425,16 @@ def pld_score_both(hidden, attn, lens, cand_pos, cand_count, workspace_h, worksp
                    agg=PLD_AGG_SUM, threshold_h=float("-inf"), threshold_a=float("-inf"),
                    scores_h=None, scores_a=None, stream=None, prepare=False):
     """pld_score_hidden and pld_score_attn of the same occurrences in one launch."""
-    import torch
-    _need(hidden, torch.bfloat16, "hidden", 3)
-    _need(attn, torch.float32, "attn", 3)
-    _need(cand_pos, torch.int32, "cand_pos", 2)
+    torch = _torch or _th()
+    hs = _need(hidden, torch.bfloat16, "hidden", 3)
+    as_ = _need(attn, torch.float32, "attn", 3)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
     B, n_rows, d = hidden.shape
     _, R, n_keys = attn.shape
     return _run("pld_score_both", (
-        _ptr(hidden), hidden.stride(0), hidden.stride(1), n_rows, d,
-        _ptr(attn), attn.stride(0), attn.stride(1), n_keys, R, int(agg),
-        _ptr(lens), _ptr(cand_pos), cand_pos.stride(0), _ptr(cand_count), B,
+        _ptr(hidden), hs[0], hs[1], n_rows, d,
+        _ptr(attn), as_[0], as_[1], n_keys, R, int(agg),
+        _ptr(lens), _ptr(cand_pos), cs[0], _ptr(cand_count), B,
         float(threshold_h), float(threshold_a), _ptr(scores_h), _ptr(scores_a),
         _ptr(workspace_h), _nbytes(workspace_h), _ptr(workspace_a), _nbytes(workspace_a),
         _stream(stream)), prepare)
@@ -437,12 +452,12 @@ def pld_select_draft(tokens, lens, K, best_pos, best_score, draft, draft_len, wo
     """Selection and draft in one launch: keys in `workspace` -> best_pos / best_score and
     draft [B][K] / draft_len [B]; a second ranking's keys in `aux_workspace` (optional) ->
     aux_best_pos / aux_best_score."""
-    import torch
-    _need(tokens, torch.int32, "tokens", 2)
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
     _need(draft, torch.int32, "draft", 2)
     if draft.shape[1] != K or draft.stride(0) != K:
         raise TypeError("draft must be a contiguous [B][K] tensor")
-    return _run("pld_select_draft", (_ptr(tokens), tokens.stride(0), _ptr(lens), tokens.shape[0],
+    return _run("pld_select_draft", (_ptr(tokens), ts[0], _ptr(lens), tokens.shape[0],
           K, _ptr(best_pos), _ptr(best_score), _ptr(draft), _ptr(draft_len), _ptr(workspace),
           _nbytes(workspace), _ptr(aux_workspace), _nbytes(aux_workspace), _ptr(aux_best_pos),
           _ptr(aux_best_score), _stream(stream),), prepare)
@@ -450,18 +465,18 @@ def pld_select_draft(tokens, lens, K, best_pos, best_score, draft, draft_len, wo
 
 def pld_verify_argmax(logits, draft_len, workspace, stream=None, prepare=False):
     """Row maxima of the K+1 logits rows (rows past each draft skipped) into the workspace."""
-    import torch
+    torch = _torch or _th()
     if logits.dtype not in (torch.float32, torch.bfloat16):
         raise TypeError("logits must be float32 or bfloat16")
-    _need(logits, logits.dtype, "logits", 3)
+    ls = _need(logits, logits.dtype, "logits", 3)
     B, K1, V = logits.shape
     dtype = PLD_F32 if logits.dtype == torch.float32 else PLD_BF16
-    return _run("pld_verify_argmax", (_ptr(logits), dtype, logits.stride(0), logits.stride(1), V, K1 - 1,
+    return _run("pld_verify_argmax", (_ptr(logits), dtype, ls[0], ls[1], V, K1 - 1,
           _ptr(draft_len), B, _ptr(workspace), _nbytes(workspace), _stream(stream),), prepare)
 
 
 def _sample_shapes(logits, draft, uniforms, out_tokens, row_sample):
-    import torch
+    torch = _torch or _th()
     if logits.dtype not in (torch.float32, torch.bfloat16):
         raise TypeError("logits must be float32 or bfloat16")
     _need(logits, logits.dtype, "logits", 3)
