@@ -46,6 +46,7 @@ struct SampleArgs {
     int32_t *row_sample;   // [B][K+1] or null
     float2 *stats;         // [B][K+1][nseg_max]: (segment maximum, mass relative to it)
     int parts;             // finishing blocks per sequence (rows split between them)
+    bool pair;             // two parts that hand over one word (sample_finish_kernel)
     int32_t *tickets;      // [B], zero on entry and exit: the parts that are done
     int32_t *tokens;       // [B][K+1]: the parts' tokens, handed to the last part
 };
@@ -127,8 +128,14 @@ __device__ __forceinline__ float seg_weight(float2 st, float M, float k) {
 //     ballot and a walk through one vector's elements.
 // Where rounding leaves no crossing, the last element with mass is taken, so
 // the token always has nonzero fp32 probability.  With one part the tokens go
-// to LDS and, after a barrier, one wave runs the acceptance.  With several,
-// each token goes to the workspace by an atomic exchange whose return is
+// to LDS and, after a barrier, one wave runs the acceptance.  With two (up to 32
+// rows) and a vocabulary of up to 2^25, a part finds where its own rows stop --
+// the first whose token is not the draft's, or row L -- and exchanges that row and
+// its token, in one word, with the sequence's zeroed counter: the part that finds
+// the other's word there has the earlier of the two, the accepted length and the
+// model's token, and writes the outputs.  One trip to memory instead of three (us
+// per call: 4 sequences of 32 fp32 rows of 32000 12.9 -> 12.4, 64 of 17 bf16 rows
+// 22.2 -> 21.6, of 128256 55.8 -> 55.2).  Otherwise, each token goes to the workspace by an atomic exchange whose return is
 // waited for, each part then counts itself done with one atomic add on the
 // sequence's counter, and the part that brings it to the number of parts
 // reads the tokens back by atomics, returns the counter to zero and runs the
@@ -344,7 +351,7 @@ __global__ __launch_bounds__(kFinishWaves *kWave) void sample_finish_kernel(Samp
             if (i + nw < r1 && i + nw <= L) next = load_row_inputs<kBf16>(a, b, i + nw);
             const int y = sample_row<kBf16>(a, b, i, in);
             if (lane == 0) {
-                if (a.parts == 1) {
+                if (a.parts == 1 || a.pair) {
                     s_y[i] = y;
                 } else {
                     // handed over by an atomic, whose return is waited for: the
@@ -360,6 +367,39 @@ __global__ __launch_bounds__(kFinishWaves *kWave) void sample_finish_kernel(Samp
     if (rs)
         for (int i = max(r0, ok ? L + 1 : 0) + (int)threadIdx.x; i < r1; i += (int)blockDim.x)
             rs[i] = -1;
+    if (a.pair) {
+        lds_barrier();
+        if (w != 0) return;
+        // Where this part's rows stop: 1 << 31 | row << 25 | token (row K + 1 where
+        // none of them does).
+        uint32_t stop = (1u << 31) | ((uint32_t)(K + 1) << 25);
+        const int i = r0 + lane;   // at most 16 rows
+        const bool mine = ok && i < r1 && i <= L;
+        const int32_t y = mine ? s_y[i] : -1;
+        const uint64_t at = __ballot(mine && (i == L || y != dr[min(i, K - 1)]));
+        if (at) {
+            const int f = __ffsll((unsigned long long)at) - 1;
+            stop = (1u << 31) | ((uint32_t)(r0 + f) << 25) | (uint32_t)__shfl(y, f);
+        }
+        uint32_t other = 0;
+        if (lane == 0) {
+            other = (uint32_t)atomicExch(a.tickets + b, (int)stop);
+            if (other) atomicExch(a.tickets + b, 0);   // zero again for the next call
+        }
+        other = (uint32_t)__builtin_amdgcn_readfirstlane((int)other);
+        if (!other) return;   // the other part writes the outputs
+        stop = min(stop, other);
+        const int acc = (int)((stop >> 25) & 63u);
+        const int32_t y_acc = (int32_t)(stop & ((1u << 25) - 1u));
+        int32_t *out = a.out_tokens + (int64_t)b * (K + 1);
+        for (int r = lane; r <= K; r += kWave)
+            out[r] = !ok ? -1 : (r < acc ? dr[r] : (r == acc ? y_acc : -1));
+        if (lane == 0) {
+            a.accept_len[b] = ok ? acc : -1;
+            a.out_count[b] = ok ? acc + 1 : 0;
+        }
+        return;
+    }
     if (a.parts > 1) {
         // The last part to finish runs the acceptance.  The tokens travel by
         // atomics only (no cache maintenance): every part's exchanges have
@@ -431,6 +471,7 @@ static int prep_sample(const void *logits, int dtype, int64_t l_seq_stride, int6
     a.tokens = a.tickets + align_up((size_t)B * sizeof(int32_t), 256) / sizeof(int32_t);
     // finishing parts: every row of a sequence in the first round of a part's waves
     a.parts = (K + 1 + kFinishWaves - 1) / kFinishWaves;
+    a.pair = a.parts == 2 && V <= (1 << 25);
     // Statistics blocks per row: about PLD_VERIFY_TARGET_BLOCKS in all, and
     // no more waves per row than the row has segments.
     const int64_t rows = (int64_t)B * (K + 1);
