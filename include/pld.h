@@ -407,8 +407,8 @@ int pld_verify_sample_finish(const void *logits, int dtype, int64_t l_seq_stride
  *                 [0, T-2]; entries past cand_count are not written
  * Device-side rules: a count outside [0, cap] counts as 0; a sequence with
  * T < 2 or T > tok_stride gets best_pos = -1, best_score = -inf.
- * Cost: one 256-thread block per sequence, one trip to memory per 16 matched
- * tokens of a candidate, so a sequence takes about cand_count / 256 rounds
+ * Cost: one 1024-thread block per sequence, one trip to memory per 16 matched
+ * tokens of a candidate, so a sequence takes about cand_count / 1024 rounds
  * of ceil(m / 16) trips: made for the lists of a decoding step (thousands of
  * candidates), not for lists of millions.
  * Errors: PLD_ERR_INVALID (NULL, B outside [1, 65535], tok_stride or cap out
@@ -419,6 +419,24 @@ int pld_select_prefix(const int32_t *tokens, int64_t tok_stride, const int32_t *
                       const int32_t *cand_pos, int64_t cap, const int32_t *cand_count, int B,
                       int max_match, float *scores, int32_t *best_pos, float *best_score,
                       void *stream);
+
+/*
+ * pld_draft_prefix -- prompt lookup's drafting in one call: pld_find_candidates,
+ * then pld_select_prefix over its list, then pld_emit_draft (the same outputs,
+ * bit for bit).  One launch for tok_stride <= 16384; past that the find call's
+ * launches and one more.
+ *
+ *   tokens ... ngram_max, cand_pos, cap, cand_count, ngram_used, scratch
+ *                          as pld_find_candidates
+ *   max_match, scores, best_pos, best_score   as pld_select_prefix
+ *   K, draft, draft_len    as pld_emit_draft
+ * Errors: the union of the three calls' errors (nothing is launched on one).
+ */
+int pld_draft_prefix(const int32_t *tokens, int64_t tok_stride, const int32_t *lens, int B,
+                     int ngram_min, int ngram_max, int max_match, int K, int32_t *cand_pos,
+                     int64_t cap, int32_t *cand_count, int32_t *ngram_used, float *scores,
+                     int32_t *best_pos, float *best_score, int32_t *draft, int32_t *draft_len,
+                     void *scratch, size_t scratch_bytes, void *stream);
 
 /*
  * pld_commit -- the step after verification in the generation loop: the

@@ -24,7 +24,8 @@ __all__ = [
     "pld_score_attn", "pld_select_best", "pld_select_draft", "pld_verify_argmax",
     "pld_verify_accept",
     "pld_verify_sample", "pld_verify_sample_workspace_bytes", "pld_verify_sample_stats",
-    "pld_verify_sample_finish", "PLD_MAX_SAMPLE_ROWS", "pld_select_prefix", "pld_commit", "pld_accept_commit",
+    "pld_verify_sample_finish", "PLD_MAX_SAMPLE_ROWS", "pld_select_prefix", "pld_draft_prefix",
+    "pld_commit", "pld_accept_commit",
     "PLD_MAX_MATCH",
 ]
 
@@ -82,6 +83,8 @@ _SIGNATURES = {
                                   ctypes.c_double, _vp, _i64, _vp, _vp, _vp, _vp, _vp, _sz, _vp],
                                  _int),
     "pld_select_prefix": ([_vp, _i64, _vp, _vp, _i64, _vp, _int, _int, _vp, _vp, _vp, _vp], _int),
+    "pld_draft_prefix": ([_vp, _i64, _vp, _int, _int, _int, _int, _int, _vp, _i64, _vp, _vp, _vp,
+                          _vp, _vp, _vp, _vp, _vp, _sz, _vp], _int),
     "pld_commit": ([_vp, _i64, _vp, _vp, _vp, _vp, _int, _int, _vp, _vp], _int),
     "pld_accept_commit": ([_vp, _vp, _int, _int, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _vp, _vp,
                            _sz, _vp], _int),
@@ -319,6 +322,22 @@ def pld_select_prefix(tokens, lens, cand_pos, cand_count, best_pos, best_score, 
     return _run("pld_select_prefix", (_ptr(tokens), ts[0], _ptr(lens), _ptr(cand_pos),
           cs[0], _ptr(cand_count), tokens.shape[0], int(max_match), _ptr(scores),
           _ptr(best_pos), _ptr(best_score), _stream(stream),), prepare)
+
+
+def pld_draft_prefix(tokens, lens, ngram_min, ngram_max, max_match, K, cand_pos, cand_count,
+                     ngram_used, best_pos, best_score, draft, draft_len, scratch=None, scores=None,
+                     stream=None, prepare=False):
+    """pld_find_candidates, pld_select_prefix and pld_emit_draft in one call (the same outputs)."""
+    torch = _torch or _th()
+    ts = _need(tokens, torch.int32, "tokens", 2)
+    cs = _need(cand_pos, torch.int32, "cand_pos", 2)
+    _need(draft, torch.int32, "draft", 2)
+    if draft.shape[1] != K or draft.stride(0) != K:
+        raise TypeError("draft must be a contiguous [B][K] tensor")
+    return _run("pld_draft_prefix", (_ptr(tokens), ts[0], _ptr(lens), tokens.shape[0], ngram_min,
+          ngram_max, int(max_match), K, _ptr(cand_pos), cs[0], _ptr(cand_count), _ptr(ngram_used),
+          _ptr(scores), _ptr(best_pos), _ptr(best_score), _ptr(draft), _ptr(draft_len),
+          _ptr(scratch), _nbytes(scratch), _stream(stream),), prepare)
 
 
 def pld_commit(tokens, lens, out_tokens, out_count, limit=None, stats=None, stream=None,

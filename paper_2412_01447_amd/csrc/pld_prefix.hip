@@ -7,17 +7,20 @@
 // the chosen j* has the largest m, the earliest among equal lengths (prompt
 // lookup scans the context from the start and keeps the first match).
 //
-// One block per sequence.  The query suffix x[T-1], x[T-2], ... is staged in
-// LDS; each lane takes a candidate and compares 16 tokens back at a time with
-// independent loads (one trip to memory per 16 matched tokens, not one per
-// token).  The choice is the maximum of the packed key (m << 32 | ~j) over the
-// block, by DPP wave maxima.
+// Rows of up to 16384 tokens are drafted in one launch (draft_prefix_kernel): the
+// search leaves the token row and the list in LDS, where the match lengths are
+// taken and the draft is read.  Nothing but the token row is read from memory, and
+// what bounds the step is launches: as the separate calls it took three, the
+// second and third waiting for a few KB of the one before.  Longer rows are
+// searched by the find call's launches, and one more selects and writes the draft.
 #include "pld.h"
 #include "pld_device.h"
+#include "pld_match.h"
 
 namespace pld {
 
-constexpr int kPrefixThreads = 256;
+constexpr int kPrefixThreads = 1024;
+constexpr int kPrefixWaves = kPrefixThreads / kWave;
 constexpr int kPrefixChunk = 16;   // tokens compared per trip to memory
 
 struct PrefixArgs {
@@ -32,11 +35,53 @@ struct PrefixArgs {
     float *scores;   // [B][cap] or null
     int32_t *best_pos;
     float *best_score;
+    int K;           // 0: no draft
+    int32_t *draft;
+    int32_t *draft_len;
 };
 
+// The match length of candidate j (0 <= j <= T-2), x in global memory or LDS:
+// `query(k)` gives x[T-1-k] for k < qn.  kPrefixChunk tokens back at a time with
+// independent loads, one trip to memory per chunk matched.
+template <class QueryToken>
+__device__ __forceinline__ int match_length(const int32_t *x, int64_t j, int qn, QueryToken query) {
+    // the run can reach back to x[0] and no further than the query suffix
+    const int lim = (int)min((int64_t)qn, j + 1);
+    int m = 0;
+    bool run = true;
+    while (run && m < lim) {
+        int32_t v[kPrefixChunk];
+#pragma unroll
+        for (int k = 0; k < kPrefixChunk; ++k) v[k] = x[max(j - m - k, (int64_t)0)];
+#pragma unroll
+        for (int k = 0; k < kPrefixChunk; ++k) {
+            if (run && m < lim && v[k] == query(m)) ++m;
+            else run = false;
+        }
+    }
+    return m;
+}
+
+__device__ __forceinline__ uint64_t prefix_key(int m, int64_t j) {
+    return ((uint64_t)(uint32_t)m << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
+}
+
+// The block's best key as the ranking's (score, position) key, in every thread;
+// `s_key` is one word per wave.
+__device__ __forceinline__ uint64_t block_choice(uint64_t best, uint64_t *s_key) {
+    best = wave_max_u64(best);
+    if (lane_id() == 0) s_key[threadIdx.x / kWave] = best;
+    lds_barrier();
+    const uint64_t k = wave_max_u64(lane_id() < kPrefixWaves ? s_key[lane_id()] : 0ull);
+    return k ? rank_key((float)(uint32_t)(k >> 32), (int32_t)(0xffffffffu - (uint32_t)k)) : 0ull;
+}
+
+// One block per sequence over a list in memory.  The query suffix is staged in
+// LDS; a lane takes a candidate.  1024 threads, so that the few thousand
+// candidates of a long context are few dependent rounds (position, tokens).
 __global__ __launch_bounds__(kPrefixThreads) void select_prefix_kernel(PrefixArgs a) {
     __shared__ int32_t s_q[PLD_MAX_MATCH];   // x[T-1-k]
-    __shared__ uint64_t s_key[kPrefixThreads / kWave];
+    __shared__ uint64_t s_key[kPrefixWaves];
     const int b = blockIdx.x;
     const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
     const int64_t T = a.lens[b];
@@ -53,36 +98,74 @@ __global__ __launch_bounds__(kPrefixThreads) void select_prefix_kernel(PrefixArg
         const int64_t j = pos[c];
         float s = NAN;
         if (j >= 0 && j <= T - 2) {
-            // the run can reach back to x[0] and no further than the query suffix
-            const int lim = (int)min((int64_t)qn, j + 1);
-            int m = 0;
-            bool run = true;
-            while (run && m < lim) {
-                int32_t v[kPrefixChunk];
-#pragma unroll
-                for (int k = 0; k < kPrefixChunk; ++k) v[k] = x[max(j - m - k, (int64_t)0)];
-#pragma unroll
-                for (int k = 0; k < kPrefixChunk; ++k) {
-                    if (run && m < lim && v[k] == s_q[m]) ++m;
-                    else run = false;
-                }
-            }
+            const int m = match_length(x, j, qn, [&](int k) { return s_q[k]; });
             s = (float)m;
-            const uint64_t key = ((uint64_t)(uint32_t)m << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
+            const uint64_t key = prefix_key(m, j);
             best = key > best ? key : best;
         }
         if (a.scores) a.scores[(int64_t)b * a.cap + c] = s;
     }
-    best = wave_max_u64(best);
-    if (lane_id() == 0) s_key[threadIdx.x / kWave] = best;
+    best = block_choice(best, s_key);
+    if (threadIdx.x < kWave)
+        write_choice_draft(best, T, seq_ok, x, a.K, a.best_pos + b, a.best_score + b,
+                           a.K ? a.draft + (int64_t)b * a.K : nullptr,
+                           a.K ? a.draft_len + b : nullptr);
+}
+
+struct DraftPrefixArgs {
+    PrefixArgs p;        // cand_pos and cand_count unused
+    int nmin, nmax;
+    int32_t *cand_pos;
+    int32_t *cand_count;
+    int32_t *ngram_used;
+};
+
+// One block per sequence, tok_stride <= kPasses * kFindFusedMax: the search of the
+// one-block find, its list in LDS as well, then a lane per candidate.
+template <int kPasses>
+__global__ __launch_bounds__(kPrefixThreads) void draft_prefix_kernel(DraftPrefixArgs d) {
+    static_assert(kPrefixWaves == kFindWavesFused, "the search takes the whole block");
+    constexpr int G = kPasses * kFindFusedMax / kPrefixThreads;
+    __shared__ __align__(16) int32_t s_x[kPasses * kFindFusedMax];
+    __shared__ int32_t s_list[kPasses * kFindFusedMax];
+    __shared__ int s_lvl[kPrefixWaves][kMaxNgram];
+    __shared__ uint64_t s_key[kPrefixWaves];
+    const PrefixArgs &a = d.p;
+    const int b = blockIdx.x;
+    const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
+    // the whole token row is requested with the length, not after it
+    const int64_t T = a.lens[b];
+    if (((uintptr_t)x & 15) == 0 && (a.tok_stride & 3) == 0)
+        copy_to_lds(reinterpret_cast<const uint4 *>(x), reinterpret_cast<uint4 *>(s_x),
+                    (int)(a.tok_stride / 4));
+    else
+        stage_tokens(x, 0, a.tok_stride, s_x);
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    const bool tok_ok = T >= 1 && T <= a.tok_stride;   // block-uniform
+    int n_used = -1, total = 0;
+    if (tok_ok)
+        n_used = block_search<kPrefixWaves, G>(s_x, T, d.nmin, d.nmax, s_lvl, s_list, total);
+    lds_barrier();   // the list is complete
     if (threadIdx.x == 0) {
-        uint64_t k = s_key[0];
-#pragma unroll
-        for (int w = 1; w < kPrefixThreads / kWave; ++w) k = s_key[w] > k ? s_key[w] : k;
-        a.best_pos[b] = k ? (int32_t)(0xffffffffu - (uint32_t)k) : -1;
-        a.best_score[b] = k ? (float)(uint32_t)(k >> 32) : -INFINITY;
+        d.cand_count[b] = total;
+        d.ngram_used[b] = n_used;
     }
+    // every listed position lies in [1, T-2]
+    const int qn = tok_ok ? (int)min((int64_t)a.max_match, T) : 0;
+    uint64_t best = 0;
+    for (int c = threadIdx.x; c < total; c += kPrefixThreads) {
+        const int32_t j = s_list[c];
+        d.cand_pos[(int64_t)b * a.cap + c] = j;
+        const int m = match_length(s_x, j, qn, [&](int k) { return s_x[T - 1 - k]; });
+        const uint64_t key = prefix_key(m, j);
+        best = key > best ? key : best;
+        if (a.scores) a.scores[(int64_t)b * a.cap + c] = (float)m;
+    }
+    best = block_choice(best, s_key);
+    if (threadIdx.x < kWave)
+        write_choice_draft(best, T, tok_ok, s_x, a.K, a.best_pos + b, a.best_score + b,
+                           a.draft + (int64_t)b * a.K, a.draft_len + b);
 }
 
 }  // namespace pld
@@ -99,8 +182,42 @@ extern "C" int pld_select_prefix(const int32_t *tokens, int64_t tok_stride, cons
         return PLD_ERR_INVALID;
     if (max_match < 1 || max_match > PLD_MAX_MATCH) return PLD_ERR_INVALID;
     PrefixArgs a{tokens, tok_stride, lens, cand_pos, cap, cand_count, B, max_match,
-                 scores,  best_pos,   best_score};
+                 scores,  best_pos,   best_score, 0, nullptr, nullptr};
     hipLaunchKernelGGL(select_prefix_kernel, dim3((unsigned)B), dim3(kPrefixThreads), 0,
                        (hipStream_t)stream, a);
+    return hipGetLastError() == hipSuccess ? PLD_OK : PLD_ERR_LAUNCH;
+}
+
+extern "C" int pld_draft_prefix(const int32_t *tokens, int64_t tok_stride, const int32_t *lens,
+                                int B, int ngram_min, int ngram_max, int max_match, int K,
+                                int32_t *cand_pos, int64_t cap, int32_t *cand_count,
+                                int32_t *ngram_used, float *scores, int32_t *best_pos,
+                                float *best_score, int32_t *draft, int32_t *draft_len,
+                                void *scratch, size_t scratch_bytes, void *stream) {
+    if (!tokens || !lens || !cand_pos || !cand_count || !ngram_used || !best_pos || !best_score ||
+        !draft || !draft_len)
+        return PLD_ERR_INVALID;
+    if (B < 1 || B > 65535 || tok_stride < 1 || tok_stride > kMaxTokStride) return PLD_ERR_INVALID;
+    if (ngram_min < 1 || ngram_max < ngram_min || ngram_max > PLD_MAX_NGRAM) return PLD_ERR_INVALID;
+    if (cap < tok_stride || K < 1) return PLD_ERR_INVALID;
+    if (max_match < 1 || max_match > PLD_MAX_MATCH) return PLD_ERR_INVALID;
+    if (((int64_t)B * K + 255) / 256 > 0x7fffffff) return PLD_ERR_INVALID;   // as pld_emit_draft
+    const PrefixArgs a{tokens, tok_stride, lens, cand_pos, cap, cand_count, B, max_match,
+                       scores,  best_pos,   best_score, K, draft, draft_len};
+    const hipStream_t s = (hipStream_t)stream;
+    const dim3 grid((unsigned)B), threads(kPrefixThreads);
+    if (tok_stride <= kFindFusedPasses * kFindFusedMax) {
+        const DraftPrefixArgs d{a, ngram_min, ngram_max, cand_pos, cand_count, ngram_used};
+        if (tok_stride <= kFindFusedMax)
+            hipLaunchKernelGGL(draft_prefix_kernel<1>, grid, threads, 0, s, d);
+        else
+            hipLaunchKernelGGL(draft_prefix_kernel<kFindFusedPasses>, grid, threads, 0, s, d);
+    } else {
+        const int rc = pld_find_candidates(tokens, tok_stride, lens, B, ngram_min, ngram_max,
+                                           cand_pos, cap, cand_count, ngram_used, scratch,
+                                           scratch_bytes, stream);
+        if (rc != PLD_OK) return rc;
+        hipLaunchKernelGGL(select_prefix_kernel, grid, threads, 0, s, a);
+    }
     return hipGetLastError() == hipSuccess ? PLD_OK : PLD_ERR_LAUNCH;
 }

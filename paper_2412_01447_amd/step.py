@@ -10,7 +10,7 @@ import torch
 
 from . import (DRAFT_MAX_PART, DRAFT_MAX_TOK_STRIDE, PLD_AGG_SUM, PLD_BF16, PLD_F32,
                PLD_MAX_DRAFT_SPLIT, pld_accept_commit, pld_commit, pld_draft_attn, pld_draft_hidden,
-               pld_draft_workspace_bytes, pld_emit_draft, pld_find_candidates,
+               pld_draft_prefix, pld_draft_workspace_bytes, pld_emit_draft, pld_find_candidates,
                pld_find_scratch_bytes, pld_rank_attn, pld_rank_hidden, pld_score_attn,
                pld_score_both, pld_score_hidden, pld_select_best, pld_select_draft, pld_select_prefix,
                pld_verify_accept,
@@ -252,9 +252,8 @@ class DraftStep:
         With both artifacts, the hidden-state ranking drafts and the attention ranking
         is written to best_pos_attn / best_score_attn."""
         if prefix_match is not None:
-            self.find(tokens, lens, *ngram, stream=stream)
-            self.select_prefix(tokens, lens, prefix_match, stream=stream)
-            self.emit(tokens, lens, stream=stream)
+            self._prefix_drafting(tokens, lens, ngram, prefix_match,
+                                  dict(stream=stream, prepare=False))
             return
         if self.uses_fused(hidden, attn):
             self.draft_fused(tokens, lens, hidden, attn, ngram, agg, threshold, stream=stream)
@@ -262,6 +261,12 @@ class DraftStep:
         # (unprepared: each call is issued as the list is built)
         self._split_drafting(tokens, lens, hidden, attn, ngram, agg, threshold,
                              dict(stream=stream, prepare=False))
+
+    def _prefix_drafting(self, tokens, lens, ngram, max_match, P):
+        """Prompt lookup's find, selection and draft, in one call."""
+        return pld_draft_prefix(tokens, lens, ngram[0], ngram[1], max_match, self.K, self.cand_pos,
+                                self.cand_count, self.ngram_used, self.best_pos, self.best_score,
+                                self.draft, self.draft_len, self.scratch, scores=self.scores, **P)
 
     def _split_drafting(self, tokens, lens, hidden, attn, ngram, agg, threshold, P):
         """The separate calls of the drafting half: find, the scoring of each artifact,
@@ -303,21 +308,13 @@ class DraftStep:
     def plan(self, tokens, lens, logits, hidden=None, attn=None, ngram=(1, 1), agg=PLD_AGG_SUM,
              threshold=float("-inf"), prefix_match=None, commit=None, stream=None):
         """The step as an ordered list of (name, prepared call), one kernel per entry
-        except "find" on long contexts (two): the same work as run(), with every
+        except "find" and prompt lookup's "draft" on long contexts: the same work as run(), with every
         argument marshalled once so that issuing a step costs only the launches.
         commit=(limit, stats) adds the commit of the generation loop (with greedy
         verification, fused into the acceptance's launch: pld_accept_commit)."""
         P = dict(stream=stream, prepare=True)
         if prefix_match is not None:
-            ops = [("find", pld_find_candidates(tokens, lens, ngram[0], ngram[1], self.cand_pos,
-                                                self.cand_count, self.ngram_used, self.scratch,
-                                                **P)),
-                   ("select_prefix", pld_select_prefix(tokens, lens, self.cand_pos,
-                                                       self.cand_count, self.best_pos,
-                                                       self.best_score, prefix_match,
-                                                       scores=self.scores, **P)),
-                   ("emit", pld_emit_draft(tokens, lens, self.best_pos, self.K, self.draft,
-                                           self.draft_len, **P))]
+            ops = [("draft", self._prefix_drafting(tokens, lens, ngram, prefix_match, P))]
         elif self.uses_fused(hidden, attn):
             if hidden is not None:
                 d = pld_draft_hidden(tokens, lens, ngram[0], ngram[1], hidden, self.K,

@@ -288,6 +288,14 @@ def test_prefix_and_commit_host_validation():
     assert sp(F, 100, F, F, 0, F, 2, 4, NULL, F, F, NULL) == E_INV
     assert sp(F, 100, F, F, 100, F, 2, 0, NULL, F, F, NULL) == E_INV
     assert sp(F, 100, F, F, 100, F, 2, pld.PLD_MAX_MATCH + 1, NULL, F, F, NULL) == E_INV
+    dp = lib.pld_draft_prefix
+    ok = (F, 100, F, 2, 1, 2, 4, 8, F, 100, F, F, NULL, F, F, F, F, NULL, 0, NULL)
+    for k in (0, 2, 8, 10, 11, 13, 14, 15, 16):   # required pointers
+        assert dp(*(ok[:k] + (NULL,) + ok[k + 1:])) == E_INV, k
+    for k, bad in ((1, 0), (1, 2**30 + 1), (3, 0), (3, 65536), (4, 0), (5, 0), (5, 9), (6, 0),
+                   (6, pld.PLD_MAX_MATCH + 1), (7, 0), (9, 99)):
+        assert dp(*(ok[:k] + (bad,) + ok[k + 1:])) == E_INV, (k, bad)
+    assert dp(*(ok[:1] + (16385,) + ok[2:9] + (16385,) + ok[10:])) == pld.PLD_ERR_WORKSPACE
     cm = lib.pld_commit
     assert cm(NULL, 100, F, NULL, F, F, 2, 4, NULL, NULL) == E_INV
     assert cm(F, 100, F, NULL, F, F, 0, 4, NULL, NULL) == E_INV

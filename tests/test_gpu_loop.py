@@ -89,6 +89,45 @@ def test_select_prefix_arbitrary_positions_and_fig3():
         assert list(gs[0, :fcc[0]]) == e[f"match_len_max{cap_m}"] and gb[0] == e[f"best_pos_max{cap_m}"]
 
 
+@pytest.mark.parametrize("T", [1, 63, 300, 8192, 8193, 16384, 16385, 70001])
+def test_draft_prefix_is_the_three_calls(T):
+    """One-call prompt lookup at the edges of its forms (one launch up to 16384 tokens,
+    of one or two search passes; the tiled search past that): every output equals the
+    separate calls' and the oracle's, misaligned rows and invalid lengths included."""
+    say("draft_prefix", T)
+    rng = np.random.default_rng(T)
+    B, K = 6, 9
+    toks = rng.integers(0, 30, size=(B, T)).astype(np.int32)
+    toks[3] = 5                                  # every position occurs, runs past the cap
+    lens = np.array([T, max(T - 1, 1), (T + 1) // 2, T, 0, T + 1], np.int32)
+    for src in (T // 3, T // 2):                 # copies of the query's context
+        ln = min(40, src + 1, T - 1 - src)
+        if ln > 0:
+            toks[0, src - ln + 1:src + 1] = toks[0, T - ln:]
+    for (nmin, nmax), mm in (((1, 1), 64), ((1, 3), 3), ((2, 4), 1), ((1, 8), 1024)):
+        got = []
+        for one in (True, False):
+            step = DraftStep(B, T, K, device=dev(), keep_scores=True)
+            step.scores.fill_(-7.0)
+            x, n = d_i32(toks), d_i32(lens)
+            if one:
+                step.make_draft(x, n, ngram=(nmin, nmax), prefix_match=mm)
+            else:
+                step.find(x, n, nmin, nmax)
+                step.select_prefix(x, n, mm)
+                step.emit(x, n)
+            got.append(step.host())
+        g, w = got
+        for name in g:
+            assert np.array_equal(g[name], w[name], equal_nan=True), (name, nmin, nmax, mm)
+        cp, cc, nu = oracle.find(toks, lens, nmin, nmax)
+        assert np.array_equal(g["cand_count"], cc) and np.array_equal(g["ngram_used"], nu)
+        r = oracle.select_prefix(toks, lens, cp, cc, mm)
+        check_prefix((g["scores"], g["best_pos"], g["best_score"]), r, cc, f"{nmin, nmax, mm}")
+        dr, dl = oracle.emit(toks, lens, r[1], K)
+        assert np.array_equal(g["draft"], dr) and np.array_equal(g["draft_len"], dl)
+
+
 def test_commit_parity():
     """Appends under limits and row capacity, invalid lengths and counts left
     alone, counters accumulated over two calls; every byte of the rows checked."""
