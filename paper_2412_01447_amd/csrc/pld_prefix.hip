@@ -21,7 +21,8 @@ namespace pld {
 
 constexpr int kPrefixThreads = 1024;
 constexpr int kPrefixWaves = kPrefixThreads / kWave;
-constexpr int kPrefixChunk = 16;   // tokens compared per trip to memory
+constexpr int kPrefixChunk = 16;      // tokens compared per trip to memory
+constexpr int kPrefixChunkLds = 4;    // and to LDS
 
 struct PrefixArgs {
     const int32_t *tokens;
@@ -40,25 +41,53 @@ struct PrefixArgs {
     int32_t *draft_len;
 };
 
-// The match length of candidate j (0 <= j <= T-2), x in global memory or LDS:
-// `query(k)` gives x[T-1-k] for k < qn.  kPrefixChunk tokens back at a time with
-// independent loads, one trip to memory per chunk matched.
-template <class QueryToken>
+// Compares the kChunk tokens back from x[j-m] with the query's from x[T-1-m],
+// advancing m to the first difference or to lim; whether the run goes on.  Loads
+// that would reach below x[0] are clamped (their tokens lie past lim <= j + 1).
+template <int kChunk, bool kGlobal, class QueryToken>
+__device__ __forceinline__ bool match_chunk(const int32_t *x, int64_t j, int lim, QueryToken query,
+                                            int &m) {
+    int32_t v[kChunk];
+    const int64_t at = j - m;
+    if (kGlobal && at >= kChunk - 1) {
+        typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+        for (int g = 0; g < kChunk / 4; ++g) {
+            const i32x4 t = *reinterpret_cast<const i32x4 *>(x + at - 4 * g - 3);
+            v[4 * g] = t.w;
+            v[4 * g + 1] = t.z;
+            v[4 * g + 2] = t.y;
+            v[4 * g + 3] = t.x;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kChunk; ++k) v[k] = x[max(at - k, (int64_t)0)];
+    }
+    const int m0 = m;
+    bool run = true;
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) {
+        run = run && m0 + k < lim && v[k] == query(m0 + k);
+        m += run ? 1 : 0;
+    }
+    return run;
+}
+
+// The match length of candidate j (0 <= j <= T-2), x in global memory (kGlobal) or
+// LDS; `query(k)` gives x[T-1-k] for k < qn, any value past that.  What bounds the
+// lanes' scattered reads of memory is the addresses that a CU's load path takes,
+// about one a clock: 16 tokens in four 16-byte loads, not sixteen (4 x 100000
+// tokens, 2500 occurrences: 40.5 -> 26.5 us per step).  In LDS most candidates
+// end within four tokens (per step, 16 | 8 | 4 at a time: 8 x 4096 tokens 14.3 | 14.7 |
+// 14.0 us, 48 x 16384 29.3 | 28.8 | 28.2).
+template <bool kGlobal, class QueryToken>
 __device__ __forceinline__ int match_length(const int32_t *x, int64_t j, int qn, QueryToken query) {
     // the run can reach back to x[0] and no further than the query suffix
     const int lim = (int)min((int64_t)qn, j + 1);
     int m = 0;
     bool run = true;
-    while (run && m < lim) {
-        int32_t v[kPrefixChunk];
-#pragma unroll
-        for (int k = 0; k < kPrefixChunk; ++k) v[k] = x[max(j - m - k, (int64_t)0)];
-#pragma unroll
-        for (int k = 0; k < kPrefixChunk; ++k) {
-            if (run && m < lim && v[k] == query(m)) ++m;
-            else run = false;
-        }
-    }
+    while (run && m < lim)
+        run = match_chunk<kGlobal ? kPrefixChunk : kPrefixChunkLds, kGlobal>(x, j, lim, query, m);
     return m;
 }
 
@@ -80,7 +109,7 @@ __device__ __forceinline__ uint64_t block_choice(uint64_t best, uint64_t *s_key)
 // LDS; a lane takes a candidate.  1024 threads, so that the few thousand
 // candidates of a long context are few dependent rounds (position, tokens).
 __global__ __launch_bounds__(kPrefixThreads) void select_prefix_kernel(PrefixArgs a) {
-    __shared__ int32_t s_q[PLD_MAX_MATCH];   // x[T-1-k]
+    __shared__ int32_t s_q[PLD_MAX_MATCH + kPrefixChunk];   // x[T-1-k]
     __shared__ uint64_t s_key[kPrefixWaves];
     const int b = blockIdx.x;
     const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
@@ -98,7 +127,7 @@ __global__ __launch_bounds__(kPrefixThreads) void select_prefix_kernel(PrefixArg
         const int64_t j = pos[c];
         float s = NAN;
         if (j >= 0 && j <= T - 2) {
-            const int m = match_length(x, j, qn, [&](int k) { return s_q[k]; });
+            const int m = match_length<true>(x, j, qn, [&](int k) { return s_q[k]; });
             s = (float)m;
             const uint64_t key = prefix_key(m, j);
             best = key > best ? key : best;
@@ -157,7 +186,7 @@ __global__ __launch_bounds__(kPrefixThreads) void draft_prefix_kernel(DraftPrefi
     for (int c = threadIdx.x; c < total; c += kPrefixThreads) {
         const int32_t j = s_list[c];
         d.cand_pos[(int64_t)b * a.cap + c] = j;
-        const int m = match_length(s_x, j, qn, [&](int k) { return s_x[T - 1 - k]; });
+        const int m = match_length<false>(s_x, j, qn, [&](int k) { return s_x[max((int)T - 1 - k, 0)]; });
         const uint64_t key = prefix_key(m, j);
         best = key > best ? key : best;
         if (a.scores) a.scores[(int64_t)b * a.cap + c] = (float)m;
