@@ -498,7 +498,7 @@ int pld_accept_commit(const int32_t *draft, const int32_t *draft_len, int B, int
  *                     launch compacts the lists and writes the selection and
  *                     the draft (with ngram_min < ngram_max a counting launch
  *                     comes first).  Spreads long contexts and long lists
- *                     over S x B blocks.  With tok_stride <= 8192, a batch
+ *                     over S x B blocks.  With tok_stride <= 16384, a batch
  *                     whose S blocks per sequence roughly fit on the GPU
  *                     together takes one launch instead, up to S blocks
  *                     sharing a sequence's occurrences.

@@ -3,7 +3,7 @@
 // hidden-state cosine (Eq. 2) or aggregated attention (Eq. 3, Sec. 7.1),
 // selection of the best occurrence, and the draft span (Sec. 4.3).
 //
-// tok_stride <= 8192, S == 1 or a team of up to S blocks: a 1024-thread block
+// S == 1 (tok_stride <= 8192) or a team of up to S blocks (<= 16384): a 1024-thread block
 //   copies the token row and the query row into LDS, finds the occurrences
 //   (the one-block search of the find call, listing them in LDS), scores its
 //   share of them with the same per-row routines as the separate ranking calls
@@ -193,7 +193,7 @@ __device__ void write_draft(const DraftArgs &a, int b, int64_t T, bool tok_ok, u
                        a.draft + (int64_t)b * a.K, a.draft_len + b);
 }
 
-// ------------------------------------------------- rows of up to 8192 tokens
+// ------------------------------------------------ rows of up to 16384 tokens
 // A team of blocks per sequence: each searches the whole row (from L2 after the
 // first; the search of 8192 tokens takes a block about a microsecond), so each
 // knows the list and its share of it, no list is compacted, and the block that
@@ -205,25 +205,41 @@ __device__ void write_draft(const DraftArgs &a, int b, int64_t T, bool tok_ok, u
 // d = 4096 13.6 | 13.1 | 12.7, 10 x 4096, 100, d = 1024 18.6 | 14.5 | 15.3, 2 x 2048,
 // 30, d = 8192 13.9 | 13.2 | 12.7, 1 x 8192, 800, d = 4096 13.9 | 13.9 | 14.6 (the
 // split form: 17.0, 18.4, 15.9, 17.2); scored by one block up to 64 KB, against
-// 128 KB: the same or faster.  Attention: 16 to 64 candidates per block within 2%.
+// 128 KB: the same or faster.
+// Attention's scattered weights each take an address of the CU's load path, and few
+// of their lines are in flight per CU, so a sequence is one block's up to 2048
+// weights, not up to a number of candidates (up to 256 candidates | 2048 weights, us
+// per step: 4 x 6000 tokens, 64 heads 20.7 | 14.6, 4 x 8192, 32 heads 17.1 | 14.0, 12 x
+// 3000, 32 heads 17.0 | 14.8; 1024 or 4096 weights within 0.3).  Past that 16 to 64
+// candidates per block lie within 2%.
+// Rows of 8193 to 16384 tokens take a second search pass, about a microsecond, and
+// save the finishing launch too (split | team): hidden, 4 x 16384, d = 4096 18.9 |
+// 17.2, with n = 3..1 25.0 | 19.5, 8 x 12000, d = 2048 20.2 | 18.1, 6 ragged of 9001,
+// d = 5120, n = 2..1 24.4 | 18.6, 16 x 10000, d = 4096 22.0 | 21.4; attention, 4 x 16384
+// 16.3 | 15.4, 8 x 16000 18.2 | 17.0, 16 x 16384 18.8 | 18.1.
 constexpr int kTeamMax = 128;             // blocks per sequence
+constexpr int kTeamPasses = 2;            // search passes of the longest rows, 16384 tokens
+// whose tokens and list leave this much of a CU's LDS for the query row
+constexpr size_t kTeamQueryMax = 163840 - 2 * 4 * kTeamPasses * kFindFusedMax - 1024;
 constexpr int kTeamBytes = 65536;         // hidden: rows' bytes per block, 4 to 8 rows
-constexpr int kAloneGathers = 256, kTeamGathers = 32;   // attention: candidates
+constexpr int kAloneGathers = 2048, kTeamGathers = 32;   // attention: weights; candidates
 // Blocks of a team of `most` that share the scoring of `total` candidates.
 template <bool kHidden>
 __device__ __forceinline__ int team_size(const DraftArgs &a, int total, int most) {
     if (most == 1) return 1;
-    if (kHidden ? (int64_t)total * a.d * 2 <= kTeamBytes : total <= kAloneGathers) return 1;
+    if (kHidden ? (int64_t)total * a.d * 2 <= kTeamBytes : (int64_t)total * a.R <= kAloneGathers)
+        return 1;
     const int share = kHidden ? max(4, min(8, kTeamBytes / (2 * a.d))) : kTeamGathers;
     return min(most, (total + share - 1) / share);
 }
 
-template <bool kHidden, int kRows, int kLoads>
+// kPasses search passes: tok_stride <= kPasses * kFindFusedMax.
+template <bool kHidden, int kRows, int kLoads, int kPasses>
 __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArgs a) {
     constexpr int kWaves = kFindWavesFused;
     constexpr int kThreads = kWaves * kWave;
-    __shared__ __align__(16) int32_t s_buf[kFindFusedMax];   // the tokens
-    __shared__ int32_t s_list[kFindFusedMax];                // the occurrence list
+    __shared__ __align__(16) int32_t s_buf[kPasses * kFindFusedMax];   // the tokens
+    __shared__ int32_t s_list[kPasses * kFindFusedMax];                // the occurrence list
     extern __shared__ uint4 s_q[];                           // query row H[T-2] (hidden)
     __shared__ int s_lvl[kWaves][kMaxNgram];
     __shared__ uint64_t s_key[kWaves];
@@ -251,8 +267,8 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
     // ---- occurrences (Eq. 1), longest n first, listed in LDS
     int n_used = -1, total = 0;
     if (tok_ok)   // block-uniform
-        n_used = block_search<kWaves, kFindFusedMax / (kWaves * kWave)>(s_buf, T, a.nmin, a.nmax,
-                                                                        s_lvl, s_list, total);
+        n_used = block_search<kWaves, kPasses * kFindFusedMax / kThreads>(s_buf, T, a.nmin, a.nmax,
+                                                                          s_lvl, s_list, total);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();   // the list and the query row are complete
     if (part == 0 && threadIdx.x == 0) {
@@ -709,27 +725,31 @@ static DraftArgs make_draft(const int32_t *tokens, int64_t tok_stride, const int
 template <bool kHidden, int kRows, int kLoads>
 static void launch_draft_as(const DraftArgs &a, hipStream_t s) {
     const size_t lds = kHidden ? (size_t)(a.d / 8) * sizeof(uint4) : 0;
-    // Rows of up to 8192 tokens: one block per sequence, or a team of as many as
+    // Rows of up to 16384 tokens: one block per sequence, or a team of as many as
     // asked for and fit on the GPU together, unless a sequence's share of the GPU
     // is so much less than the blocks asked for that the slices of the split form,
     // four blocks per CU, balance the batch's lists better.  Measured (us per
     // step, team | split; S asked for, `fit` blocks per sequence resident):
     // hidden, 16 x 8192 (S 34, fit 16) 25.9 | 28.7, 24 x 8192 (S 37, fit 10) 35.8 |
-    // 32.0; attention, 12 x 3000 (S 28, fit 21) 12.8 | 16.4, 16 x 8192 (S 34, fit 16)
-    // 19.7 | 18.8, 32 x 8192 (S 40, fit 8) 30.1 | 27.7.
+    // 32.0; attention, 16 x 8192 (S 34, fit 16) 17.4 | 20.3, 24 x 4000 (S 24, fit 10)
+    // 17.3 | 20.5, 32 x 8192 (S 40, fit 8) 26.3 | 27.6, 48 x 4000 (S 19, fit 5) 22.7 |
+    // 26.0; two attention blocks per CU (64 registers): 12 x 3000 14.8 -> 16.6, 24 x 4000
+    // 17.3 -> 18.6.
+    const bool one = a.tok_stride <= kFindFusedMax;   // search passes
+    void (*const kernel)(DraftArgs) = one ? &draft_kernel<kHidden, kRows, kLoads, 1>
+                                          : &draft_kernel<kHidden, kRows, kLoads, kTeamPasses>;
     int team = a.S == 1 ? 1 : 0;
-    if (a.S > 1 && a.tok_stride <= kFindFusedMax) {
-        const int fit = resident_blocks(
-            reinterpret_cast<const void *>(&draft_kernel<kHidden, kRows, kLoads>),
-            kFindWavesFused * kWave, lds) / a.B;
-        if (2 * a.S <= (kHidden ? 5 : 3) * fit) {
+    if (a.S > 1 && a.tok_stride <= kTeamPasses * kFindFusedMax &&
+        (one || lds <= kTeamQueryMax)) {
+        const int fit = resident_blocks(reinterpret_cast<const void *>(kernel),
+                                        kFindWavesFused * kWave, lds) / a.B;
+        if (2 * a.S <= (kHidden ? 5 : 12) * fit) {
             team = a.S < fit ? a.S : fit;
             if (team > kTeamMax) team = kTeamMax;
         }
     }
     if (team > 0) {
-        hipLaunchKernelGGL((draft_kernel<kHidden, kRows, kLoads>), dim3(team, a.B),
-                           dim3(kFindWavesFused * kWave), lds, s, a);
+        hipLaunchKernelGGL(kernel, dim3(team, a.B), dim3(kFindWavesFused * kWave), lds, s, a);
         return;
     }
     if (a.nmin < a.nmax)

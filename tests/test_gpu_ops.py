@@ -1010,32 +1010,36 @@ def test_draft_finish_limits_past_the_team(split):
 @pytest.mark.parametrize("d,R,total", [(512, 0, 64), (512, 0, 65), (512, 0, 1000), (4096, 0, 8),
                                        (4096, 0, 9), (4096, 0, 45), (8192, 0, 5), (9000, 0, 23),
                                        (64, 0, 3000), (0, 5, 256), (0, 5, 257), (0, 70, 1000),
-                                       (0, 3, 4094)])
-def test_draft_team(d, R, total):
+                                       (0, 3, 4094), (0, 5, 409), (0, 5, 410), (0, 70, 29),
+                                       (0, 70, 30)])
+def test_draft_team(d, R, total, T=4096):
     """A team of blocks drafting one sequence: lists at the sizes where a block stops
-    scoring alone (64 KB of rows, 256 attention candidates), with shares of
+    scoring alone (64 KB of rows, 2048 attention weights), with shares of
     unequal length, more blocks asked for than have a share, an empty list, one
     longer than the others, an invalid length, no eligible candidate, n-gram
     ranges; two calls in turn on one workspace; the same bits as the separate
     calls."""
-    say("draft team", d, R, total)
-    B, T, K = 4, 4096, 6
+    say("draft team", d, R, total, T)
+    B, K = 4, 6
     rng = np.random.default_rng(d + R + total)
     toks = rng.integers(1, 1 << 20, size=(B, T)).astype(np.int32)
     lens = np.array([T, T, T - 1, T + 1], np.int32)
     for b, n in ((0, total), (2, min(total, 11))):
         toks[b, 1 + rng.choice(lens[b] - 2, n, replace=False)] = 0
         toks[b, lens[b] - 1] = 0
+    toks[1, lens[1] - 1] = 1 << 20                # occurs nowhere else
     i32 = dict(dtype=torch.int32, device="cuda")
     td, ld = d_i32(toks), d_i32(lens)
     if d:
-        art = d_bf16(synth.f32_to_bf16_bits(rng.standard_normal((B, T, d)).astype(np.float32)))
+        bits = synth.f32_to_bf16_bits(rng.standard_normal((T, d)).astype(np.float32))
+        art = d_bf16(bits[None]).expand(B, T, d) if T > 4096 else d_bf16(
+            synth.f32_to_bf16_bits(rng.standard_normal((B, T, d)).astype(np.float32)))
     else:
         art = d_f32(rng.random((B, R, T), dtype=np.float32))
     for nmin, nmax in ((1, 1), (1, 3)):
         cp, cc, nu = oracle.find(toks, lens, nmin, nmax)
         assert cc[0] == total and cc[1] == 0 and cc[3] == 0 or nmax > 1
-        for S in (2, 3, 7, 64, 160):
+        for S in (2, 3, 7, 64, 160)[T > 16384:]:
             ws = draft_workspace(B, S)
             for th in (-math.inf, 1e9):
                 o = [torch.full((B, T), -1, **i32), torch.zeros(B, **i32), torch.zeros(B, **i32),
@@ -1059,6 +1063,23 @@ def test_draft_team(d, R, total):
                 rd, rl = oracle.emit(toks, lens, rbp, K)
                 assert np.array_equal(g[5], rd) and np.array_equal(g[6], rl), what
                 assert draft_keys_zero(ws, B), what
+
+
+@pytest.mark.parametrize("T,d,R,total", [(8192, 512, 0, 100), (8193, 512, 0, 100),
+                                         (16383, 0, 5, 500), (16384, 4096, 0, 45),
+                                         (16384, 0, 3, 16382), (16385, 512, 0, 100),
+                                         (8200, 15872, 0, 9), (8200, 15880, 0, 9)])
+def test_draft_team_two_passes(T, d, R, total):
+    """The same at the edges of the two-pass form: 8192 | 8193 and 16384 | 16385 tokens,
+    and the widest query row that its LDS holds beside the tokens and the list."""
+    test_draft_team(d, R, total, T)
+
+
+@pytest.mark.parametrize("split", [192, 240, 241, 1000])
+def test_draft_finish_limits_small_share(split):
+    """The finishing launch's limits over four sequences, whose share of the GPU is too
+    small for a team at these splits."""
+    test_draft_fused_parity((4, 15360, 1, 1, 1, 64, 0, 6, 14), split)
 
 
 def test_autotune_split_keeps_the_results():
