@@ -26,8 +26,11 @@
  *   reported through the outputs as documented per call.
  * - `workspace` (ranking and verification calls) is device memory of at
  *   least pld_workspace_bytes(B, K) bytes.  It must be zero-filled once after
- *   allocation; every call returns it to all-zero by the time its kernels
- *   complete, so one buffer serves every such call of a stream in turn.
+ *   allocation; every call returns those bytes to zero by the time its kernels
+ *   complete, so one buffer serves every such call of that B and K on a stream
+ *   in turn.  Only the sampling calls write past those bytes, and leave other
+ *   values there: before a call of a larger B or K that reaches into what they
+ *   used, fill the buffer with zeros again.
  * - `scratch` (occurrence search) is device memory of at least
  *   pld_find_scratch_bytes(B, tok_stride) bytes with no requirement on its
  *   contents; it may be NULL when that size is 0.  It must not overlap a
@@ -251,12 +254,12 @@ int pld_verify_greedy_noalloc(const void *logits, int dtype, int64_t l_seq_strid
  *   row_sample   int32 [B][K+1] or NULL: y_i for i <= L, -1 for the rows
  *                past the draft (all -1 when draft_len is out of range)
  *   workspace    at least pld_verify_sample_workspace_bytes(B, K, V, dtype)
- *                bytes, zero-filled once like every workspace; its first
- *                pld_workspace_bytes(B, K) bytes are left zero by the call,
- *                then come per-call statistics, B counters that every call
- *                leaves zero (K+1 > 16: the blocks that share a sequence's
- *                rows count themselves done there, the last one accepting)
- *                and the tokens those blocks hand over, rewritten each time.
+ *                bytes; its first pld_workspace_bytes(B, K) bytes are not
+ *                touched (zero for the other calls that share the buffer).
+ *                Nothing is asked of the rest: the statistics, one counter per
+ *                sequence, which the statistics pass zeroes, and the tokens
+ *                that the blocks sharing a sequence's rows hand over.  So one
+ *                buffer serves calls of several vocabularies and types.
  * Arithmetic: the masses are fp32 (2^((z - m) * log2(e)/tau)) and are summed
  * per 512-vector segment of the row, then over the segments; a row of -inf
  * gives y = 0, and where rounding leaves no element past the target the last

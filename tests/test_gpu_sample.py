@@ -177,6 +177,33 @@ def test_verify_sample_finish_block_borders(K):
         check_sample(_rows_fn(Z, False), 1.0, U, draft, L, got, ref, f"K{K} call {call}")
 
 
+@pytest.mark.parametrize("K", [15, 16, 31, 32, 40])
+def test_verify_sample_one_workspace_for_several_shapes(K):
+    """One buffer serves vocabularies and types in turn: where a sequence's counter
+    lies depends on both, so a call finds another's statistics there, or (the first
+    call) arbitrary bytes past the shared zero part; two calls of each shape."""
+    say("verify_sample shapes in turn", K)
+    B = 5
+    rng = np.random.default_rng(900 + K)
+    shapes = ((40001, False), (1001, False), (1001, True), (40001, True), (9000, False))
+    ws = torch.full((max(sample_workspace(B, K, V, bf).numel() for V, bf in shapes),), 0x3c,
+                    dtype=torch.uint8, device="cuda")
+    ws[:pld.pld_workspace_bytes(B, K)] = 0
+    for V, bf16 in shapes:
+        for call in range(2):
+            Z = (rng.standard_normal((B, K + 1, V)) * 2.0).astype(np.float32)
+            L = np.array([K, min(16, K), K - 1, -1, int(rng.integers(0, K + 1))], np.int32)
+            draft = rng.integers(0, V, size=(B, K)).astype(np.int32)
+            for b in range(B):
+                for i in range(int(rng.integers(0, K + 1))):
+                    Z[b, i, draft[b, i]] = 30.0      # all the mass on the draft token
+            U = rng.random((B, K + 1), dtype=np.float32)
+            zb = synth.f32_to_bf16_bits(Z) if bf16 else Z
+            ref = oracle.verify_sample(zb, draft, L, 1.0, U, bf16=bf16)
+            got = gpu_verify_sample(d_bf16(zb) if bf16 else d_f32(Z), draft, L, 1.0, U, ws=ws)
+            check_sample(_rows_fn(zb, bf16), 1.0, U, draft, L, got, ref, f"V{V} call {call}")
+
+
 def test_verify_sample_at_the_most_rows():
     """K + 1 = PLD_MAX_SAMPLE_ROWS rows per sequence: 1024 finishing blocks per
     sequence hand their tokens to the last one.  A full acceptance, a draft
