@@ -19,9 +19,9 @@
 
 namespace pld {
 
-constexpr int kPrefixThreads = 1024;
+constexpr int kPrefixThreads = 1024;  // the one-launch form
 constexpr int kPrefixWaves = kPrefixThreads / kWave;
-constexpr int kPrefixChunk = 16;      // tokens compared per trip to memory
+constexpr int kPrefixChunk = 16;      // tokens compared per trip to memory (at most)
 constexpr int kPrefixChunkLds = 4;    // and to LDS
 
 struct PrefixArgs {
@@ -73,21 +73,20 @@ __device__ __forceinline__ bool match_chunk(const int32_t *x, int64_t j, int lim
     return run;
 }
 
-// The match length of candidate j (0 <= j <= T-2), x in global memory (kGlobal) or
-// LDS; `query(k)` gives x[T-1-k] for k < qn, any value past that.  What bounds the
+// The match length of candidate j (0 <= j <= T-2), kChunk tokens at a time, x in
+// global memory (kGlobal) or LDS; `query(k)` gives x[T-1-k] for k < qn, any value past that.  What bounds the
 // lanes' scattered reads of memory is the addresses that a CU's load path takes,
 // about one a clock: 16 tokens in four 16-byte loads, not sixteen (4 x 100000
 // tokens, 2500 occurrences: 40.5 -> 26.5 us per step).  In LDS most candidates
 // end within four tokens (per step, 16 | 8 | 4 at a time: 8 x 4096 tokens 14.3 | 14.7 |
 // 14.0 us, 48 x 16384 29.3 | 28.8 | 28.2).
-template <bool kGlobal, class QueryToken>
+template <int kChunk, bool kGlobal, class QueryToken>
 __device__ __forceinline__ int match_length(const int32_t *x, int64_t j, int qn, QueryToken query) {
     // the run can reach back to x[0] and no further than the query suffix
     const int lim = (int)min((int64_t)qn, j + 1);
     int m = 0;
     bool run = true;
-    while (run && m < lim)
-        run = match_chunk<kGlobal ? kPrefixChunk : kPrefixChunkLds, kGlobal>(x, j, lim, query, m);
+    while (run && m < lim) run = match_chunk<kChunk, kGlobal>(x, j, lim, query, m);
     return m;
 }
 
@@ -95,22 +94,26 @@ __device__ __forceinline__ uint64_t prefix_key(int m, int64_t j) {
     return ((uint64_t)(uint32_t)m << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
 }
 
-// The block's best key as the ranking's (score, position) key, in every thread;
-// `s_key` is one word per wave.
+// The best key of a block of kWaves waves as the ranking's (score, position) key,
+// in every thread of its first wave; `s_key` is one word per wave.
+template <int kWaves>
 __device__ __forceinline__ uint64_t block_choice(uint64_t best, uint64_t *s_key) {
     best = wave_max_u64(best);
     if (lane_id() == 0) s_key[threadIdx.x / kWave] = best;
     lds_barrier();
-    const uint64_t k = wave_max_u64(lane_id() < kPrefixWaves ? s_key[lane_id()] : 0ull);
+    if (threadIdx.x >= kWave) return 0ull;
+    const uint64_t k = wave_max_u64(lane_id() < kWaves ? s_key[lane_id()] : 0ull);
     return k ? rank_key((float)(uint32_t)(k >> 32), (int32_t)(0xffffffffu - (uint32_t)k)) : 0ull;
 }
 
 // One block per sequence over a list in memory.  The query suffix is staged in
-// LDS; a lane takes a candidate.  1024 threads, so that the few thousand
-// candidates of a long context are few dependent rounds (position, tokens).
-__global__ __launch_bounds__(kPrefixThreads) void select_prefix_kernel(PrefixArgs a) {
+// LDS; a lane takes a candidate, kChunk tokens at a time.  launch_select_prefix
+// picks the form.
+template <int kThreads, int kChunk>
+__global__ __launch_bounds__(kThreads) void select_prefix_kernel(PrefixArgs a) {
+    static_assert(kChunk <= kPrefixChunk, "s_q is read up to kChunk - 1 past the suffix");
     __shared__ int32_t s_q[PLD_MAX_MATCH + kPrefixChunk];   // x[T-1-k]
-    __shared__ uint64_t s_key[kPrefixWaves];
+    __shared__ uint64_t s_key[kThreads / kWave];
     const int b = blockIdx.x;
     const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
     const int64_t T = a.lens[b];
@@ -118,23 +121,23 @@ __global__ __launch_bounds__(kPrefixThreads) void select_prefix_kernel(PrefixArg
     if (C < 0 || C > a.cap) C = 0;
     const bool seq_ok = T >= 2 && T <= a.tok_stride;   // block-uniform
     const int qn = seq_ok ? (int)min((int64_t)a.max_match, T) : 0;
-    for (int k = threadIdx.x; k < qn; k += kPrefixThreads) s_q[k] = x[T - 1 - k];
+    for (int k = threadIdx.x; k < qn; k += kThreads) s_q[k] = x[T - 1 - k];
     __syncthreads();
 
     const int32_t *pos = a.cand_pos + (int64_t)b * a.cap;
     uint64_t best = 0;
-    for (int64_t c = threadIdx.x; c < (seq_ok ? C : 0); c += kPrefixThreads) {
+    for (int64_t c = threadIdx.x; c < (seq_ok ? C : 0); c += kThreads) {
         const int64_t j = pos[c];
         float s = NAN;
         if (j >= 0 && j <= T - 2) {
-            const int m = match_length<true>(x, j, qn, [&](int k) { return s_q[k]; });
+            const int m = match_length<kChunk, true>(x, j, qn, [&](int k) { return s_q[k]; });
             s = (float)m;
             const uint64_t key = prefix_key(m, j);
             best = key > best ? key : best;
         }
         if (a.scores) a.scores[(int64_t)b * a.cap + c] = s;
     }
-    best = block_choice(best, s_key);
+    best = block_choice<kThreads / kWave>(best, s_key);
     if (threadIdx.x < kWave)
         write_choice_draft(best, T, seq_ok, x, a.K, a.best_pos + b, a.best_score + b,
                            a.K ? a.draft + (int64_t)b * a.K : nullptr,
@@ -186,15 +189,37 @@ __global__ __launch_bounds__(kPrefixThreads) void draft_prefix_kernel(DraftPrefi
     for (int c = threadIdx.x; c < total; c += kPrefixThreads) {
         const int32_t j = s_list[c];
         d.cand_pos[(int64_t)b * a.cap + c] = j;
-        const int m = match_length<false>(s_x, j, qn, [&](int k) { return s_x[max((int)T - 1 - k, 0)]; });
+        const int m = match_length<kPrefixChunkLds, false>(
+            s_x, j, qn, [&](int k) { return s_x[max((int)T - 1 - k, 0)]; });
         const uint64_t key = prefix_key(m, j);
         best = key > best ? key : best;
         if (a.scores) a.scores[(int64_t)b * a.cap + c] = (float)m;
     }
-    best = block_choice(best, s_key);
+    best = block_choice<kPrefixWaves>(best, s_key);
     if (threadIdx.x < kWave)
         write_choice_draft(best, T, tok_ok, s_x, a.K, a.best_pos + b, a.best_score + b,
                            a.draft + (int64_t)b * a.K, a.draft_len + b);
+}
+
+// Up to 256 sequences there is a CU for each, and 1024 threads make the few thousand
+// candidates of a long context few dependent rounds (position, tokens); up to 512,
+// two blocks of 512 threads share one.  Past that what bounds the call is how many
+// short lists a CU takes at once: 256 threads, whose 8-token chunks need fewer
+// registers than 16 (4 | 8 | 16 tokens in the 1024-thread form, 4 x 100000 tokens,
+// every one of 2500 occurrences matching 64: 24.3 | 20.9 | 18.8 us).  Measured (us per
+// call, 1024 threads | 512 | 256 of 16-token chunks | 256 of 8): 256 x 16384 tokens, 256
+// occurrences each 4.6 | 4.4 | 5.2 | -, 2048 each 7.9 | 9.6 | 12.8 | -; 512 x 4096, 4 each
+// 5.4 | 3.9 | 3.7 | -, 512 x 16384, 2048 each 13.5 | 10.9 | 14.7 | -; 2048 x 4096, 64
+// each 22.9 | 10.6 | 7.4 | 6.1, 4096 x 4096, 4 each 34.1 | 14.4 | 7.8 | 6.5, 65535 x 128, 8
+// each 646 | 231 | 98 | 77.
+static void launch_select_prefix(const PrefixArgs &a, hipStream_t s) {
+    const dim3 grid((unsigned)a.B);
+    if (a.B <= 256)
+        hipLaunchKernelGGL((select_prefix_kernel<1024, 16>), grid, dim3(1024), 0, s, a);
+    else if (a.B <= 512)
+        hipLaunchKernelGGL((select_prefix_kernel<512, 16>), grid, dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((select_prefix_kernel<256, 8>), grid, dim3(256), 0, s, a);
 }
 
 }  // namespace pld
@@ -212,8 +237,7 @@ extern "C" int pld_select_prefix(const int32_t *tokens, int64_t tok_stride, cons
     if (max_match < 1 || max_match > PLD_MAX_MATCH) return PLD_ERR_INVALID;
     PrefixArgs a{tokens, tok_stride, lens, cand_pos, cap, cand_count, B, max_match,
                  scores,  best_pos,   best_score, 0, nullptr, nullptr};
-    hipLaunchKernelGGL(select_prefix_kernel, dim3((unsigned)B), dim3(kPrefixThreads), 0,
-                       (hipStream_t)stream, a);
+    launch_select_prefix(a, (hipStream_t)stream);
     return hipGetLastError() == hipSuccess ? PLD_OK : PLD_ERR_LAUNCH;
 }
 
@@ -246,7 +270,7 @@ extern "C" int pld_draft_prefix(const int32_t *tokens, int64_t tok_stride, const
                                            cand_pos, cap, cand_count, ngram_used, scratch,
                                            scratch_bytes, stream);
         if (rc != PLD_OK) return rc;
-        hipLaunchKernelGGL(select_prefix_kernel, grid, threads, 0, s, a);
+        launch_select_prefix(a, s);
     }
     return hipGetLastError() == hipSuccess ? PLD_OK : PLD_ERR_LAUNCH;
 }

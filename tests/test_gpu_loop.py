@@ -69,6 +69,28 @@ def test_select_prefix_parity(B, T, V, nmin, nmax, seed):
         check_prefix(gpu_select_prefix(toks, lens, cp, cc, mm), r, cc, f"max_match {mm}")
 
 
+@pytest.mark.parametrize("B", [256, 257, 512, 513])
+def test_select_prefix_at_the_batches_of_its_forms(B):
+    """The batches at which the block's threads and the tokens per trip to memory change:
+    lists longer than the smallest block, matches that end before, at and after a trip
+    of 8 or 16 tokens and at the start of the row, ragged and invalid lengths."""
+    say("select_prefix forms", B)
+    rng = np.random.default_rng(B)
+    T = 700
+    toks = rng.integers(0, 2, size=(B, T)).astype(np.int32)
+    lens = rng.integers(1, T + 1, size=B).astype(np.int32)
+    lens[:4] = [T, 0, T + 1, T]
+    for b in (0, 3):
+        for src in (4, 60, 200, 301):                # copies of 1 to 40 tokens of the context
+            ln = min(int(rng.integers(1, 41)), src + 1)
+            toks[b, src - ln + 1:src + 1] = toks[b, T - ln:T]
+    cp, cc, _ = oracle.find(toks, lens, 1, 1)
+    assert cc.max() > 256
+    for mm in (1, 7, 8, 9, 16, 17, 64):
+        r = oracle.select_prefix(toks, lens, cp, cc, mm)
+        check_prefix(gpu_select_prefix(toks, lens, cp, cc, mm), r, cc, f"B{B} max_match {mm}")
+
+
 def test_select_prefix_arbitrary_positions_and_fig3():
     """Candidates outside [0, T-2] score NaN and are never chosen; counts past
     cap count as 0; the Fig. 3 fixture gives prompt lookup's choice, f's span."""

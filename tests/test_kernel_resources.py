@@ -1,0 +1,51 @@
+"""Blocks per CU that the launch rules count on, from the built library's kernel metadata."""
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2412_01447_amd.build import LIB
+
+TOOLS = "/opt/rocm/llvm/bin/"
+VGPRS = 512         # per lane and SIMD of a CU, given out in eights
+LDS = 160 * 1024    # bytes per CU
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{name: (vgprs, spilled, static LDS bytes, threads per block)} of every kernel."""
+    d = tmp_path_factory.mktemp("code")
+    so = shutil.copy(LIB, d)
+    subprocess.run([TOOLS + "llvm-objdump", "--offloading", so], check=True, cwd=d,
+                   capture_output=True)
+    out = {}
+    for f in sorted(d.glob("*gfx950*")):
+        text = subprocess.run([TOOLS + "llvm-readelf", "--notes", str(f)], check=True,
+                              capture_output=True, text=True).stdout
+        # one list item per kernel; its own keys are sorted and indented by four
+        for k in re.split(r"\n  - (?=\.)", text)[1:]:
+            get = lambda key: re.search(r"^ *(?:- )?\.%s: +(\S+)" % key, k, re.M).group(1)
+            name = re.sub(r"^_ZN3pld\d+(\w+?)E+v?N.*$", r"\1", get("name"))
+            out[name] = tuple(int(get(x)) for x in (
+                "vgpr_count", "vgpr_spill_count", "group_segment_fixed_size",
+                "max_flat_workgroup_size"))
+    return out
+
+
+def blocks_per_cu(k, dynamic_lds=0):
+    vgprs, _, lds, threads = k
+    waves_per_simd = min(8, VGPRS // ((vgprs + 7) // 8 * 8))
+    return min(waves_per_simd * 4 // (threads // 64), LDS // max(1, lds + dynamic_lds))
+
+
+def test_no_kernel_spills(kernels):
+    assert len(kernels) > 50
+    assert {n: k for n, k in kernels.items() if k[1]} == {}
+
+
+def test_prompt_lookup_blocks_per_cu(kernels):
+    """Large batches: two blocks of the 1024- and four of the 512-thread selection per CU,
+    eight of the 256-thread one."""
+    sel = {k[3]: blocks_per_cu(k) for n, k in kernels.items() if "select_prefix_kernel" in n}
+    assert sel == {1024: 2, 512: 4, 256: 8}
