@@ -427,8 +427,8 @@ int pld_select_prefix(const int32_t *tokens, int64_t tok_stride, const int32_t *
 /*
  * pld_draft_prefix -- prompt lookup's drafting in one call: pld_find_candidates,
  * then pld_select_prefix over its list, then pld_emit_draft (the same outputs,
- * bit for bit).  One launch for tok_stride <= 16384; past that the find call's
- * launches and one more.
+ * bit for bit).  One launch for tok_stride <= 8192, and for tok_stride <= 16384
+ * with B <= 1024; otherwise the find call's launches and one more.
  *
  *   tokens ... ngram_max, cand_pos, cap, cand_count, ngram_used, scratch
  *                          as pld_find_candidates

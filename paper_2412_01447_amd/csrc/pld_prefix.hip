@@ -11,8 +11,9 @@
 // search leaves the token row and the list in LDS, where the match lengths are
 // taken and the draft is read.  Nothing but the token row is read from memory, and
 // what bounds the step is launches: as the separate calls it took three, the
-// second and third waiting for a few KB of the one before.  Longer rows are
-// searched by the find call's launches, and one more selects and writes the draft.
+// second and third waiting for a few KB of the one before.  Longer rows, and large
+// batches of rows past 8192 tokens, are searched by the find call's launches, and
+// one more selects and writes the draft.
 #include "pld.h"
 #include "pld_device.h"
 #include "pld_match.h"
@@ -23,6 +24,13 @@ constexpr int kPrefixThreads = 1024;  // the one-launch form
 constexpr int kPrefixWaves = kPrefixThreads / kWave;
 constexpr int kPrefixChunk = 16;      // tokens compared per trip to memory (at most)
 constexpr int kPrefixChunkLds = 4;    // and to LDS
+// Sequences up to which rows of 8193 to 16384 tokens take one launch.  Their tokens
+// and list leave a CU room for one block (131 KB of LDS), where the find call's has
+// two: past that short lists are faster as find and selection (us per step, the three
+// separate calls | one launch | two; 4, 256 and 2048 occurrences each): 1024 x 16384
+// 25.9 32.4 54.7 | 24.9 25.7 31.1 | 23.4 28.6 37.2, 2048 x 16384 46.7 58.7 97.5 | 50.5
+// 52.6 62.9 | 45.4 54.6 74.4.
+constexpr int kDraftOneLaunchB = 1024;
 
 struct PrefixArgs {
     const int32_t *tokens;
@@ -153,9 +161,14 @@ struct DraftPrefixArgs {
 };
 
 // One block per sequence, tok_stride <= kPasses * kFindFusedMax: the search of the
-// one-block find, its list in LDS as well, then a lane per candidate.
+// one-block find, its list in LDS as well, then a lane per candidate.  With one pass
+// two blocks share a CU (66 KB of LDS each; up to 64 registers, eight waves per
+// SIMD), which is what bounds large batches (us per step, the three separate calls |
+// 67 registers, one block per CU | two; 128 occurrences or fewer): 512 x 8192 14.6 |
+// 9.8 | 7.9, 4096 x 8192 64.4 | 59.5 | 40.7, 4096 x 1024 34.7 | 38.1 | 26.3, 16384 x 512
+// 115 | 141 | 93.
 template <int kPasses>
-__global__ __launch_bounds__(kPrefixThreads) void draft_prefix_kernel(DraftPrefixArgs d) {
+__global__ __launch_bounds__(kPrefixThreads, kPasses == 1 ? 8 : 4) void draft_prefix_kernel(DraftPrefixArgs d) {
     static_assert(kPrefixWaves == kFindWavesFused, "the search takes the whole block");
     constexpr int G = kPasses * kFindFusedMax / kPrefixThreads;
     __shared__ __align__(16) int32_t s_x[kPasses * kFindFusedMax];
@@ -259,7 +272,8 @@ extern "C" int pld_draft_prefix(const int32_t *tokens, int64_t tok_stride, const
                        scores,  best_pos,   best_score, K, draft, draft_len};
     const hipStream_t s = (hipStream_t)stream;
     const dim3 grid((unsigned)B), threads(kPrefixThreads);
-    if (tok_stride <= kFindFusedPasses * kFindFusedMax) {
+    if (tok_stride <= kFindFusedMax ||
+        (tok_stride <= kFindFusedPasses * kFindFusedMax && B <= kDraftOneLaunchB)) {
         const DraftPrefixArgs d{a, ngram_min, ngram_max, cand_pos, cand_count, ngram_used};
         if (tok_stride <= kFindFusedMax)
             hipLaunchKernelGGL(draft_prefix_kernel<1>, grid, threads, 0, s, d);

@@ -150,6 +150,33 @@ def test_draft_prefix_is_the_three_calls(T):
         assert np.array_equal(g["draft"], dr) and np.array_equal(g["draft_len"], dl)
 
 
+@pytest.mark.parametrize("B,T", [(300, 200), (1024, 8193), (1025, 8193), (1100, 900)])
+def test_draft_prefix_large_batches(B, T):
+    """Batches of several blocks per CU, and the batch past which rows of more than 8192
+    tokens take the find call and the selection: every output equals the separate calls'."""
+    say("draft_prefix large batch", B, T)
+    rng = np.random.default_rng(B + T)
+    toks = rng.integers(0, 12, size=(B, T)).astype(np.int32)
+    lens = rng.integers(1, T + 1, size=B).astype(np.int32)
+    lens[:4] = [T, 0, T + 1, 1]
+    x, n = d_i32(toks), d_i32(lens)
+    one, three = (DraftStep(B, T, 7, device=dev()) for _ in range(2))
+    one.make_draft(x, n, ngram=(1, 3), prefix_match=9)
+    three.find(x, n, 1, 3)
+    three.select_prefix(x, n, 9)
+    three.emit(x, n)
+    g, w = one.host(), three.host()
+    for name in g:
+        if name != "cand_pos":
+            assert np.array_equal(g[name], w[name]), name
+    for b in range(B):
+        c = g["cand_count"][b]
+        assert np.array_equal(g["cand_pos"][b, :c], w["cand_pos"][b, :c]), b
+    cp, cc, _ = oracle.find(toks[:8], lens[:8], 1, 3)
+    assert np.array_equal(g["cand_count"][:8], cc)
+    assert np.array_equal(g["best_pos"][:8], oracle.select_prefix(toks[:8], lens[:8], cp, cc, 9)[1])
+
+
 def test_commit_parity():
     """Appends under limits and row capacity, invalid lengths and counts left
     alone, counters accumulated over two calls; every byte of the rows checked."""

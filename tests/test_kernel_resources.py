@@ -46,6 +46,8 @@ def test_no_kernel_spills(kernels):
 
 def test_prompt_lookup_blocks_per_cu(kernels):
     """Large batches: two blocks of the 1024- and four of the 512-thread selection per CU,
-    eight of the 256-thread one."""
+    eight of the 256-thread one; two of the one-launch drafting of up to 8192 tokens."""
     sel = {k[3]: blocks_per_cu(k) for n, k in kernels.items() if "select_prefix_kernel" in n}
     assert sel == {1024: 2, 512: 4, 256: 8}
+    one = [blocks_per_cu(k) for n, k in kernels.items() if "draft_prefix_kernel" in n]
+    assert sorted(one) == [1, 2]
