@@ -364,10 +364,10 @@ __device__ __forceinline__ float query_norm(const uint4 *q, int nch) {
 // l+128, ... in order, pair p of a chunk into acc[p]), so a row gives the same
 // bits here as through row_dot.
 // `row(k)` gives the k-th row (k < n) of this wave, or null for an unusable
-// one (its results are reported as not valid); `begin()` runs once the first
-// two pieces are requested (the query's norm is taken there, under their
-// latency); `done(k, valid, dot, nrm)` runs in every lane when row k is
-// complete, in order of k.
+// one (its results are reported as not valid), once per row in whole-row pieces;
+// `begin()` runs once the first two pieces are requested (the query's norm is taken
+// there, under their latency); `done(k, valid, dot, nrm)` runs in every lane when
+// row k is complete, in order of k.
 template <int kRows, int kLoads, class RowPtr, class Begin, class Done>
 __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const uint4 *q,
                                             Begin begin, Done done) {
@@ -377,11 +377,13 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
     constexpr std::integral_constant<int, 1> second{};
     if constexpr (kRows > 0) {
         uint4 buf[2][kRows][kLoads];
+        bool have[2][kRows];
         auto issue = [&](auto slot, int k0) {
             constexpr int sl = decltype(slot)::value;
 #pragma unroll
             for (int g = 0; g < kRows; ++g) {
                 const uint4 *r = k0 + g < n ? row(k0 + g) : nullptr;
+                have[sl][g] = r != nullptr;
                 if (r) {
 #pragma unroll
                     for (int u = 0; u < kLoads; ++u)
@@ -392,21 +394,20 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
         auto consume = [&](auto slot, int k0) {
             constexpr int sl = decltype(slot)::value;
             float dot[kRows], nrm[kRows];
-            bool ok[kRows];
 #pragma unroll
             for (int g = 0; g < kRows; ++g) {
                 float ad[4] = {0.f, 0.f, 0.f, 0.f}, an[4] = {0.f, 0.f, 0.f, 0.f};
-                ok[g] = k0 + g < n && row(k0 + g) != nullptr;
-                if (ok[g]) {
+                if (have[sl][g]) {
 #pragma unroll
                     for (int u = 0; u < kLoads; ++u)
                         if (has(u)) accum_chunk(buf[sl][g][u], q[lane + u * kWave], ad, an);
                 }
-                finish_row(ad, an, dot[g], nrm[g]);
+                // (no sums over the lanes for the rows that a short piece lacks)
+                if (kRows == 1 || k0 + g < n) finish_row(ad, an, dot[g], nrm[g]);
             }
 #pragma unroll
             for (int g = 0; g < kRows; ++g)
-                if (k0 + g < n) done(k0 + g, ok[g], dot[g], nrm[g]);
+                if (k0 + g < n) done(k0 + g, have[sl][g], dot[g], nrm[g]);
         };
         issue(first, 0);
         issue(second, kRows);
@@ -468,7 +469,7 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
 
 // Calls f(integral_constant<kRows>, integral_constant<kLoads>) with the form
 // in which rows of width d stream, or (0, 0) past 8192 (row_dot, one row at a
-// time).  A piece holds about eight loads per lane for narrow rows, else a whole
+// time).  A piece holds a few narrow rows, four to eight loads per lane, else a whole
 // row, up to twelve loads: past that two pieces no longer fit the 128 registers
 // that keep four waves per SIMD (two 8-wave blocks per CU), and half a row is a
 // piece.  Measured as one-call
@@ -478,16 +479,19 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
 // 35.6, 4096 37.2 | 40.4 | -, 5120 41.6 | 43.6 | 43.5, 6144 47.5 | 47.9 | 48.3,
 // 7168 51.3 | 53.2 | 53.0, 8192 55.8 | 56.0 | -; but 44 x 16917 tokens with few
 // occurrences, d = 7168, take 39.2 | 35.6 | 35.6, the blocks no longer resident
-// together.  Half again as many narrow rows per
-// piece: the same or up to 1 us slower.
+// together.  Few rows to a piece keep the rows of a short list from waiting for each
+// other: d = 512 in one block per sequence, 8 x 2048 tokens with 16, 64 and 512
+// occurrences each, load-all-then-wait 6.7 8.5 32.1 | eight rows 8.3 9.8 32.8 | four
+// 5.8 7.8 29.1 | two 5.4 7.5 28.8, and the ranking call alone, 8 x 8192 with 512 each, 9.4 |
+// 11.8 | 9.3 | 9.6; d = 1024 6.9 8.9 36.0 | - | four 6.2 8.6 33.3 | two 5.6 8.1 32.8.
 template <class F>
 inline void with_row_form(int d, F f) {
     using std::integral_constant;
 #define PLD_ROW_FORM(rows, loads) \
     return f(integral_constant<int, rows>{}, integral_constant<int, loads>{})
     switch ((d + 511) / 512) {   // 16-byte loads per lane and row
-    case 1: PLD_ROW_FORM(8, 1);
-    case 2: PLD_ROW_FORM(4, 2);
+    case 1: PLD_ROW_FORM(4, 1);
+    case 2: PLD_ROW_FORM(2, 2);
     case 3: PLD_ROW_FORM(2, 3);
     case 4: PLD_ROW_FORM(2, 4);
     case 5: PLD_ROW_FORM(1, 5);

@@ -296,7 +296,7 @@ def test_rank_hidden_parity(d):
                                7168, 7680, 7688, 8184, 8192, 8200])
 def test_rank_hidden_row_load_edges(d):
     """Row widths at the edges of the streamed rows' forms (one to sixteen loads per
-    lane, eight rows to half a row per piece, the last load full or short, and the
+    lane, four rows to half a row per piece, the last load full or short, and the
     first width that does not stream): the separate call and the one-call drafting
     give the same bits, within 1e-5 of the oracle (an fp32 sum of at most 8200
     products of unit variance over norms of order sqrt(d): errors of order eps),
