@@ -205,7 +205,10 @@ __device__ void write_draft(const DraftArgs &a, int b, int64_t T, bool tok_ok, u
 // d = 4096 13.6 | 13.1 | 12.7, 10 x 4096, 100, d = 1024 18.6 | 14.5 | 15.3, 2 x 2048,
 // 30, d = 8192 13.9 | 13.2 | 12.7, 1 x 8192, 800, d = 4096 13.9 | 13.9 | 14.6 (the
 // split form: 17.0, 18.4, 15.9, 17.2); scored by one block up to 64 KB, against
-// 128 KB: the same or faster.
+// 128 KB: the same or faster.  What bounds narrow rows is their reductions, not
+// their bytes, so a block scores no more than 64 of them alone (8 x 8192 tokens, 256
+// occurrences, d = 64: up to 64 KB 17.7, up to 64 rows 8.1, the split form 11.1; one
+// block takes 6.7 for 32 rows, 7.9 for 64 and 11.6 for 128).
 // Attention's scattered weights each take an address of the CU's load path, and few
 // of their lines are in flight per CU, so a sequence is one block's up to 2048
 // weights, not up to a number of candidates (up to 256 candidates | 2048 weights, us
@@ -222,12 +225,14 @@ constexpr int kTeamPasses = 2;            // search passes of the longest rows, 
 // whose tokens and list leave this much of a CU's LDS for the query row
 constexpr size_t kTeamQueryMax = 163840 - 2 * 4 * kTeamPasses * kFindFusedMax - 1024;
 constexpr int kTeamBytes = 65536;         // hidden: rows' bytes per block, 4 to 8 rows
+constexpr int kAloneRows = 64;            // hidden: rows that one block scores alone, at most
 constexpr int kAloneGathers = 2048, kTeamGathers = 32;   // attention: weights; candidates
 // Blocks of a team of `most` that share the scoring of `total` candidates.
 template <bool kHidden>
 __device__ __forceinline__ int team_size(const DraftArgs &a, int total, int most) {
     if (most == 1) return 1;
-    if (kHidden ? (int64_t)total * a.d * 2 <= kTeamBytes : (int64_t)total * a.R <= kAloneGathers)
+    if (kHidden ? total <= kAloneRows && (int64_t)total * a.d * 2 <= kTeamBytes
+                : (int64_t)total * a.R <= kAloneGathers)
         return 1;
     const int share = kHidden ? max(4, min(8, kTeamBytes / (2 * a.d))) : kTeamGathers;
     return min(most, (total + share - 1) / share);

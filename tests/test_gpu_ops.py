@@ -1009,12 +1009,12 @@ def test_draft_finish_limits_past_the_team(split):
 
 @pytest.mark.parametrize("d,R,total", [(512, 0, 64), (512, 0, 65), (512, 0, 1000), (4096, 0, 8),
                                        (4096, 0, 9), (4096, 0, 45), (8192, 0, 5), (9000, 0, 23),
-                                       (64, 0, 3000), (0, 5, 256), (0, 5, 257), (0, 70, 1000),
+                                       (64, 0, 64), (64, 0, 65), (64, 0, 3000), (0, 5, 256), (0, 5, 257), (0, 70, 1000),
                                        (0, 3, 4094), (0, 5, 409), (0, 5, 410), (0, 70, 29),
                                        (0, 70, 30)])
 def test_draft_team(d, R, total, T=4096):
     """A team of blocks drafting one sequence: lists at the sizes where a block stops
-    scoring alone (64 KB of rows, 2048 attention weights), with shares of
+    scoring alone (64 KB of rows, 64 rows, 2048 attention weights), with shares of
     unequal length, more blocks asked for than have a share, an empty list, one
     longer than the others, an invalid length, no eligible candidate, n-gram
     ranges; two calls in turn on one workspace; the same bits as the separate
