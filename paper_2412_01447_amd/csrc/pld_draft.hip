@@ -226,6 +226,15 @@ constexpr int kTeamPasses = 2;            // search passes of the longest rows, 
 constexpr size_t kTeamQueryMax = 163840 - 2 * 4 * kTeamPasses * kFindFusedMax - 1024;
 constexpr int kTeamBytes = 65536;         // hidden: rows' bytes per block, 4 to 8 rows
 constexpr int kAloneRows = 64;            // hidden: rows that one block scores alone, at most
+// Sequences from which they lie along x of the grid, the teams along y.  Blocks go
+// round the 8 XCDs in turn, so a batch that is a multiple of 8 then has each team
+// within one XCD, whose L2 fetches its token row once; with the teams along x every
+// XCD fetches every row (us per step, split | teams along x | sequences along x; 32
+// heads): 32 x 16384 tokens, 20 occurrences 9.5 | 10.3 | 7.0, 100 each 11.3 | 12.3 | 9.6,
+// 600 each 16.3 | 17.4 | 16.0, 16 x 16384, 100 each 9.6 | 9.8 | 8.4; over 900 shapes of 8
+// to 256 sequences 8% less in the mean and at most 4% more.  Below 8 it only gathers
+// a team's scattered loads on fewer XCDs (4 x 16384, 600 each - | 8.6 | 9.6).
+constexpr int kTeamSeqXB = 8;
 constexpr int kAloneGathers = 2048, kTeamGathers = 32;   // attention: weights; candidates
 // Blocks of a team of `most` that share the scoring of `total` candidates.
 template <bool kHidden>
@@ -248,7 +257,8 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
     extern __shared__ uint4 s_q[];                           // query row H[T-2] (hidden)
     __shared__ int s_lvl[kWaves][kMaxNgram];
     __shared__ uint64_t s_key[kWaves];
-    const int part = blockIdx.x, b = blockIdx.y;
+    const bool seq_x = a.B >= kTeamSeqXB;
+    const int b = seq_x ? blockIdx.x : blockIdx.y, part = seq_x ? blockIdx.y : blockIdx.x;
     const int w = threadIdx.x / kWave;
     const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
 
@@ -280,7 +290,7 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
         a.cand_count[b] = total;
         a.ngram_used[b] = n_used;
     }
-    const int team = team_size<kHidden>(a, total, (int)gridDim.x);
+    const int team = team_size<kHidden>(a, total, (int)(seq_x ? gridDim.y : gridDim.x));
     if (part >= team) return;   // block-uniform
     uint64_t best = 0;
     if (total > 0) {   // block-uniform
@@ -738,7 +748,8 @@ static void launch_draft_as(const DraftArgs &a, hipStream_t s) {
     // hidden, 16 x 8192 (S 34, fit 16) 25.9 | 28.7, 24 x 8192 (S 37, fit 10) 35.8 |
     // 32.0; attention, 16 x 8192 (S 34, fit 16) 17.4 | 20.3, 24 x 4000 (S 24, fit 10)
     // 17.3 | 20.5, 32 x 8192 (S 40, fit 8) 26.3 | 27.6, 48 x 4000 (S 19, fit 5) 22.7 |
-    // 26.0; two attention blocks per CU (64 registers): 12 x 3000 14.8 -> 16.6, 24 x 4000
+    // 26.0, 64 x 16384 (S 24, fit 4) with 12 occurrences each 7.2 | 12.0, but with 600 each
+    // 26.0 | 24.3; two attention blocks per CU (64 registers): 12 x 3000 14.8 -> 16.6, 24 x 4000
     // 17.3 -> 18.6.
     const bool one = a.tok_stride <= kFindFusedMax;   // search passes
     void (*const kernel)(DraftArgs) = one ? &draft_kernel<kHidden, kRows, kLoads, 1>
@@ -754,7 +765,8 @@ static void launch_draft_as(const DraftArgs &a, hipStream_t s) {
         }
     }
     if (team > 0) {
-        hipLaunchKernelGGL(kernel, dim3(team, a.B), dim3(kFindWavesFused * kWave), lds, s, a);
+        hipLaunchKernelGGL(kernel, a.B >= kTeamSeqXB ? dim3(a.B, team) : dim3(team, a.B),
+                           dim3(kFindWavesFused * kWave), lds, s, a);
         return;
     }
     if (a.nmin < a.nmax)
