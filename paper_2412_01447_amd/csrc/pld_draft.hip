@@ -121,12 +121,15 @@ __device__ void draft_score_rows(const DraftArgs &a, int b, int64_t T, bool seq_
         if (a.scores && lane == 0) a.scores[(int64_t)b * a.cap + out0 + first + k * step] = s;
     };
     if constexpr (kLoads > 0) {
-        // The query's norm under the first loads' latency, unless sixteen waves
-        // have two rows or more each: their loads then fill the CU's path for
-        // longer than the norm takes, and it is ready sooner before them (30
-        // rows of 8 KB in one block: 13.4 against 13.9 us per step; 6 rows:
-        // 14.7 after the loads, 15.0 before).
-        const bool early = step == kFindWavesFused && n > kRows;
+        // The query's norm under the first loads' latency, unless each of sixteen
+        // waves has a row: their loads then fill the CU's path for longer than the
+        // norm takes, and it is ready sooner before them (us per step after the loads
+        // | before; 8 x 2048 tokens, one block each, 16 and 32 rows: d = 1024 5.6 6.5 |
+        // 5.5 6.3, 4096 6.9 8.6 | 6.6 8.1, 8192 8.5 10.7 | 8.1 10.5; blocks of a team, 4
+        // to 8 rows: 12 x 3333, d = 4096 7.7 | 7.7, 8192 8.6 | 9.1, 16 x 8192, 8192
+        // 10.2 | 10.7).
+        const int rows = total - first + (int)threadIdx.x / kWave;   // of the block
+        const bool early = step == kFindWavesFused && rows >= step;
         if (early && seq_ok) qq = query_norm(q_s, nch);
         stream_rows<kRows, kLoads>(n, nch, row, q_s, [&] {
             if (!early && seq_ok) qq = query_norm(q_s, nch);
