@@ -254,12 +254,15 @@ int pld_verify_greedy_noalloc(const void *logits, int dtype, int64_t l_seq_strid
  *   row_sample   int32 [B][K+1] or NULL: y_i for i <= L, -1 for the rows
  *                past the draft (all -1 when draft_len is out of range)
  *   workspace    at least pld_verify_sample_workspace_bytes(B, K, V, dtype)
- *                bytes; its first pld_workspace_bytes(B, K) bytes are not
- *                touched (zero for the other calls that share the buffer).
- *                Nothing is asked of the rest: the statistics, one counter per
- *                sequence, which the statistics pass zeroes, and the tokens
- *                that the blocks sharing a sequence's rows hand over.  So one
- *                buffer serves calls of several vocabularies and types.
+ *                bytes, zero-filled once like every workspace; its first
+ *                pld_workspace_bytes(B, K) bytes are not touched, the B 4-byte
+ *                counters after them are left zero (K+1 > 16: the blocks that
+ *                share a sequence's rows count themselves done there, or one of
+ *                two leaves the other the row and token at which its rows
+ *                stop), and the rest is rewritten by every call: statistics and
+ *                the tokens that three or more blocks hand over.  Where the
+ *                counters lie depends on B and K alone, so one buffer serves
+ *                calls of several vocabularies and types.
  * Arithmetic: the masses are fp32 (2^((z - m) * log2(e)/tau)) and are summed
  * per 512-vector segment of the row, then over the segments; a row of -inf
  * gives y = 0, and where rounding leaves no element past the target the last

@@ -47,7 +47,7 @@ struct SampleArgs {
     float2 *stats;         // [B][K+1][nseg_max]: (segment maximum, mass relative to it)
     int parts;             // finishing blocks per sequence (rows split between them)
     bool pair;             // two parts that hand over one word (sample_finish_kernel)
-    int32_t *tickets;      // [B], zeroed by the statistics pass: the parts that are done
+    int32_t *tickets;      // [B], zero on entry and exit: the parts that are done
     int32_t *tokens;       // [B][K+1]: the parts' tokens, handed to the last part
 };
 
@@ -57,10 +57,7 @@ __host__ __device__ __forceinline__ int seg_count(int nvec) {
 
 // One wave per segment: lane l takes vectors l, l+64, ..., l+448 of it (each
 // load instruction reads 1 KB contiguous), plus one head element (segment 0)
-// and one tail element (last segment).  Rows past the draft are not read.  The
-// first block of a sequence zeroes its counter: where the counters lie depends on
-// the vocabulary and the element type, so a call of another shape may have left
-// statistics there, which the finishing blocks would take for a hand-over.
+// and one tail element (last segment).  Rows past the draft are not read.
 template <int kBf16>
 __global__ __launch_bounds__(kVerifyThreads) void sample_stats_kernel(SampleArgs a) {
     using E = Elem<kBf16>;
@@ -68,7 +65,6 @@ __global__ __launch_bounds__(kVerifyThreads) void sample_stats_kernel(SampleArgs
     constexpr int P = E::kPerVec;
     constexpr uint32_t kNegInf2 = kBf16 ? 0xff80ff80u : 0xff800000u;   // -inf in every element
     const int i = blockIdx.y, b = blockIdx.z;
-    if (i == 0 && blockIdx.x == 0 && threadIdx.x == 0) a.tickets[b] = 0;
     const int L = a.draft_len[b];
     if (L < 0 || L > a.K || i > L) return;
     const RowView<T, P> rv = row_view<T, P>(a.logits, a.ls, a.lr, b, i, a.V);
@@ -437,10 +433,13 @@ static size_t sample_stats_bytes(int B, int K, int V, int dtype) {
     return align_up((size_t)B * ((size_t)K + 1) * (size_t)sample_nseg_max(V, dtype) * sizeof(float2),
                     256);
 }
-// [the shared zero-invariant part | statistics | tickets | tokens]
+// [the shared zero-invariant part | tickets (zero-invariant) | statistics | tokens].
+// The tickets come before the statistics, where their place depends on B and K alone:
+// past them the layout goes by the vocabulary and the type, and a word may hold the
+// statistics of a call of another vocabulary or type.
+static size_t sample_tickets_bytes(int B) { return align_up((size_t)B * sizeof(int32_t), 256); }
 static size_t sample_ws_bytes(int B, int K, int V, int dtype) {
-    return common_ws_bytes(B, K) + sample_stats_bytes(B, K, V, dtype) +
-           align_up((size_t)B * sizeof(int32_t), 256) +
+    return common_ws_bytes(B, K) + sample_tickets_bytes(B) + sample_stats_bytes(B, K, V, dtype) +
            align_up((size_t)B * ((size_t)K + 1) * sizeof(int32_t), 256);
 }
 
@@ -469,10 +468,11 @@ static int prep_sample(const void *logits, int dtype, int64_t l_seq_stride, int6
     a.k = (float)kd;
     a.draft_len = draft_len;
     char *ws = static_cast<char *>(workspace);
-    a.stats = reinterpret_cast<float2 *>(ws + common_ws_bytes(B, K));
-    a.tickets = reinterpret_cast<int32_t *>(ws + common_ws_bytes(B, K) +
-                                            sample_stats_bytes(B, K, V, dtype));
-    a.tokens = a.tickets + align_up((size_t)B * sizeof(int32_t), 256) / sizeof(int32_t);
+    ws += common_ws_bytes(B, K);
+    a.tickets = reinterpret_cast<int32_t *>(ws);
+    ws += sample_tickets_bytes(B);
+    a.stats = reinterpret_cast<float2 *>(ws);
+    a.tokens = reinterpret_cast<int32_t *>(ws + sample_stats_bytes(B, K, V, dtype));
     // finishing parts: every row of a sequence in the first round of a part's waves
     a.parts = (K + 1 + kFinishWaves - 1) / kFinishWaves;
     a.pair = a.parts == 2 && V <= (1 << 25);

@@ -166,7 +166,7 @@ __device__ __forceinline__ Accepted accept_wave(int K, int L, RowToken row_token
 }
 
 // The ranking and verification calls share the leading, zero-invariant part
-// of a workspace; the sampling statistics come after it.
+// of a workspace; the sampling calls' own regions come after it.
 inline size_t common_ws_bytes(int B, int K) {
     const size_t r = rank_ws_bytes(B);
     const size_t v = verify_ws_bytes(B, K);

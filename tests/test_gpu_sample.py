@@ -179,16 +179,16 @@ def test_verify_sample_finish_block_borders(K):
 
 @pytest.mark.parametrize("K", [15, 16, 31, 32, 40])
 def test_verify_sample_one_workspace_for_several_shapes(K):
-    """One buffer serves vocabularies and types in turn: where a sequence's counter
-    lies depends on both, so a call finds another's statistics there, or (the first
-    call) arbitrary bytes past the shared zero part; two calls of each shape."""
+    """One buffer serves vocabularies and types in turn: past the shared part and the
+    counters its layout depends on both, so a call finds another's statistics, or (the
+    first call) arbitrary bytes there; two calls of each shape."""
     say("verify_sample shapes in turn", K)
     B = 5
     rng = np.random.default_rng(900 + K)
     shapes = ((40001, False), (1001, False), (1001, True), (40001, True), (9000, False))
     ws = torch.full((max(sample_workspace(B, K, V, bf).numel() for V, bf in shapes),), 0x3c,
                     dtype=torch.uint8, device="cuda")
-    ws[:pld.pld_workspace_bytes(B, K)] = 0
+    ws[:pld.pld_workspace_bytes(B, K) + 4 * B] = 0
     for V, bf16 in shapes:
         for call in range(2):
             Z = (rng.standard_normal((B, K + 1, V)) * 2.0).astype(np.float32)
