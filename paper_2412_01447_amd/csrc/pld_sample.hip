@@ -133,9 +133,11 @@ __device__ __forceinline__ float seg_weight(float2 st, float M, float k) {
 // the first whose token is not the draft's, or row L -- and exchanges that row and
 // its token, in one word, with the sequence's zeroed counter: the part that finds
 // the other's word there has the earlier of the two, the accepted length and the
-// model's token, and writes the outputs.  One trip to memory instead of three (us
-// per call: 4 sequences of 32 fp32 rows of 32000 12.9 -> 12.4, 64 of 17 bf16 rows
-// 22.2 -> 21.6, of 128256 55.8 -> 55.2).  Otherwise, each token goes to the workspace by an atomic exchange whose return is
+// model's token, and writes the outputs.  With the draft in registers since the
+// kernel's start, that is one trip to memory instead of three (us per call, three |
+// one, but the draft read before and after it | one: 4 sequences of 32 fp32 rows of
+// 32000 12.0 | 11.4 | 11.2, 64 of 17 bf16 rows 22.8 | 22.2 | 21.9, of 128256 56.4 | 55.7 |
+// 55.5).  Otherwise, each token goes to the workspace by an atomic exchange whose return is
 // waited for, each part then counts itself done with one atomic add on the
 // sequence's counter, and the part that brings it to the number of parts
 // reads the tokens back by atomics, returns the counter to zero and runs the
@@ -376,7 +378,8 @@ __global__ __launch_bounds__(kFinishWaves *kWave) void sample_finish_kernel(Samp
         const int i = r0 + lane;   // at most 16 rows
         const bool mine = ok && i < r1 && i <= L;
         const int32_t y = mine ? s_y[i] : -1;
-        const uint64_t at = __ballot(mine && (i == L || y != dr[min(i, K - 1)]));
+        const int32_t d = __shfl(d0, i);   // draft[i]: at most 31 entries, one per lane
+        const uint64_t at = __ballot(mine && (i == L || y != d));
         if (at) {
             const int f = __ffsll((unsigned long long)at) - 1;
             stop = (1u << 31) | ((uint32_t)(r0 + f) << 25) | (uint32_t)__shfl(y, f);
@@ -391,9 +394,9 @@ __global__ __launch_bounds__(kFinishWaves *kWave) void sample_finish_kernel(Samp
         stop = min(stop, other);
         const int acc = (int)((stop >> 25) & 63u);
         const int32_t y_acc = (int32_t)(stop & ((1u << 25) - 1u));
-        int32_t *out = a.out_tokens + (int64_t)b * (K + 1);
-        for (int r = lane; r <= K; r += kWave)
-            out[r] = !ok ? -1 : (r < acc ? dr[r] : (r == acc ? y_acc : -1));
+        if (lane <= K)
+            a.out_tokens[(int64_t)b * (K + 1) + lane] =
+                !ok ? -1 : (lane < acc ? d0 : (lane == acc ? y_acc : -1));
         if (lane == 0) {
             a.accept_len[b] = ok ? acc : -1;
             a.out_count[b] = ok ? acc + 1 : 0;

@@ -177,6 +177,35 @@ def test_verify_sample_finish_block_borders(K):
         check_sample(_rows_fn(Z, False), 1.0, U, draft, L, got, ref, f"K{K} call {call}")
 
 
+@pytest.mark.parametrize("over", [0, 1])
+def test_verify_sample_at_the_largest_packed_token(over):
+    """A vocabulary of 2^25, whose last token fills the word in which the two finishing
+    blocks of 17 to 32 rows hand over their result, and one token more, where they hand
+    over tokens: each row has one finite logit, so its token is that one whatever the
+    draw; stops in either block's rows, at the draft's end and past a full acceptance."""
+    V, K, B = (1 << 25) + over, 16, 3
+    say("verify_sample largest token", V)
+    rng = np.random.default_rng(25 + over)
+    draft = rng.integers(0, V, size=(B, K)).astype(np.int32)
+    draft[:, 1::3] = V - 1
+    want = np.concatenate([draft, np.full((B, 1), V - 1, np.int32)], axis=1)
+    want[0, 12] = V - 1 if draft[0, 12] != V - 1 else 0    # sequence 0: refused in the second block
+    want[1, 4], draft[1, 4] = V - 1, 5                     # sequence 1: in the first, y = V - 1
+    L = np.array([K, K, K], np.int32)
+    z = torch.full((B, K + 1, V), -float("inf"), dtype=torch.bfloat16, device="cuda")
+    z.scatter_(2, torch.from_numpy(want).cuda().long()[:, :, None], 1.5)
+    U = rng.random((B, K + 1), dtype=np.float32)
+    got = gpu_verify_sample(z, draft, L, 1.0, U)
+    acc = np.array([12, 4, K], np.int32)
+    assert np.array_equal(got[0], acc) and np.array_equal(got[2], acc + 1)
+    assert np.array_equal(got[3], want)
+    for b in range(B):
+        out = np.full(K + 1, -1, np.int32)
+        out[:acc[b]] = draft[b, :acc[b]]
+        out[acc[b]] = want[b, acc[b]]
+        assert np.array_equal(got[1][b], out), b
+
+
 @pytest.mark.parametrize("K", [15, 16, 31, 32, 40])
 def test_verify_sample_one_workspace_for_several_shapes(K):
     """One buffer serves vocabularies and types in turn: past the shared part and the
