@@ -72,7 +72,7 @@ enum { PLD_AGG_SUM = 0, PLD_AGG_MAX = 1 };
 
 /* Version of this ABI (major * 10000 + minor * 100 + patch); pld_version()
  * returns the library's, which equals PLD_ABI_VERSION for a matching build. */
-#define PLD_ABI_VERSION 200
+#define PLD_ABI_VERSION 300
 int pld_version(void);
 
 /* A static, human-readable name for a status code. */

@@ -66,6 +66,8 @@ def test_header_compiles_as_c_and_cpp(tmp_path):
 def test_status_strings_and_version():
     m = re.search(r"#define PLD_ABI_VERSION (\d+)", open(HEADER).read())
     assert m and pld.pld_version() == int(m.group(1))
+    # a call added to the header takes a new version
+    assert (pld.pld_version(), len(_declared())) == (300, 28)
     assert pld.pld_status_string(0) == "ok"
     assert "workspace" in pld.pld_status_string(3)
     assert pld.pld_status_string(99) == "unknown status"
