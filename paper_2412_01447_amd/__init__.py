@@ -123,13 +123,18 @@ def _load():
 # two to seven a step), so it stays short: pointers and the stream travel as plain
 # integers, a tensor's strides are read once, library functions are looked up once.
 _torch = None
+_raw_stream = None   # the current device's current stream as an integer, where torch offers it
 
 
 def _th():
     """torch, imported on first use (building the library does not need it)."""
-    global _torch
+    global _torch, _raw_stream
     if _torch is None:
         import torch
+        # what torch.cuda.current_stream() wraps in an object; not public, so optional
+        get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        _raw_stream = (lambda: get(device())) if get and device else None
         _torch = torch
     return _torch
 
@@ -141,8 +146,8 @@ def _ptr(t):
 def _stream(stream):
     if stream is None:
         torch = _torch or _th()
-        if torch.cuda.is_initialized():   # what current_stream() wraps in an object
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream()
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

@@ -73,6 +73,25 @@ def test_status_strings_and_version():
     assert pld.pld_status_string(99) == "unknown status"
 
 
+@pytest.mark.parametrize("gone", ["_cuda_getCurrentRawStream", "_cuda_getDevice", None])
+def test_current_stream_without_torch_internals(monkeypatch, gone):
+    """The default stream of a call is the current one, with torch's own integer form of
+    it where that exists and through the public object where it does not."""
+    import types
+    import torch
+    if gone:
+        monkeypatch.delattr(torch._C, gone, raising=False)
+    else:
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 74 + d, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(pld, "_torch", None)
+    monkeypatch.setattr(pld, "_raw_stream", None, raising=False)
+    assert pld._stream(None) == 77
+    assert pld._stream(5) == 5 and pld._stream(types.SimpleNamespace(cuda_stream=9)) == 9
+
+
 def test_workspace_and_scratch_bytes():
     assert pld.pld_workspace_bytes(0, 4) == 0
     assert pld.pld_workspace_bytes(1, 0) == 0
