@@ -38,8 +38,10 @@ inline bool ranges_overlap(const void *p, size_t np, const void *q, size_t nq) {
 
 // Blocks of `kernel` that fit on the current device at once (CUs x resident
 // blocks per CU): the grid of the persistent kernels, whose equal contiguous
-// work ranges then finish in a single round.  Cached per device, kernel and
-// dynamic LDS size.
+// work ranges then finish in a single round.  Kept per device, kernel and
+// dynamic LDS size in a table whose slots are taken over by the latest asker, so
+// that a program of many batch sizes and widths does not run out of room and query
+// the occupancy on every call.
 inline int resident_blocks(const void *kernel, int threads, size_t dyn_lds) {
     struct Entry {
         int dev;
@@ -47,16 +49,16 @@ inline int resident_blocks(const void *kernel, int threads, size_t dyn_lds) {
         size_t lds;
         int blocks;
     };
+    constexpr size_t kSlots = 1024;
     static std::mutex mu;
-    static Entry cache[256];
-    static int used = 0;
+    static Entry table[kSlots];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    // kernel handles lie 8 bytes or more apart, the LDS sizes asked for as well
+    Entry &e = table[((uintptr_t)kernel / 8 * 67 + dyn_lds / 8 + (size_t)dev * 131) % kSlots];
     {
         std::lock_guard<std::mutex> g(mu);
-        for (int i = 0; i < used; ++i)
-            if (cache[i].dev == dev && cache[i].k == kernel && cache[i].lds == dyn_lds)
-                return cache[i].blocks;
+        if (e.k == kernel && e.lds == dyn_lds && e.dev == dev) return e.blocks;
     }
     int cus = 0, per = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -67,7 +69,7 @@ inline int resident_blocks(const void *kernel, int threads, size_t dyn_lds) {
         per = 1;
     const int blocks = cus * per;
     std::lock_guard<std::mutex> g(mu);
-    if (used < 256) cache[used++] = Entry{dev, kernel, dyn_lds, blocks};
+    e = Entry{dev, kernel, dyn_lds, blocks};
     return blocks;
 }
 

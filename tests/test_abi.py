@@ -63,6 +63,42 @@ def test_header_compiles_as_c_and_cpp(tmp_path):
         assert r.returncode == 0, r.stderr
 
 
+def test_resident_blocks_are_kept_past_any_number_of_shapes(tmp_path):
+    """The occupancy of a kernel is asked for once per shape, not on every call, also
+    after more shapes than the table holds; a shape that lost its slot is asked again."""
+    src = tmp_path / "t.hip"
+    src.write_text(r"""
+#include <cstdio>
+#include "pld_device.h"
+static int asked = 0;
+extern "C" hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+extern "C" hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+extern "C" hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t lds) {
+    ++asked;
+    *n = 1 + (int)(lds / 8 % 7);
+    return hipSuccess;
+}
+int main() {
+    const char *kernel = (const char *)0x1000;
+    for (int i = 0; i < 3000; ++i) {
+        const size_t lds = 8 * (size_t)i;
+        const int before = asked;
+        for (int call = 0; call < 3; ++call)
+            if (pld::resident_blocks(kernel + 16 * (i % 5), 256, lds) != 256 * (1 + i % 7)) return 1;
+        if (asked != before + 1) { printf("shape %d: asked %d times\n", i, asked - before); return 2; }
+    }
+    return 0;
+}
+""")
+    from paper_2412_01447_amd.build import CSRC, HIPCC
+    exe = tmp_path / "t"
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-I", CSRC,
+                        str(src), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stdout)
+
+
 def test_status_strings_and_version():
     m = re.search(r"#define PLD_ABI_VERSION (\d+)", open(HEADER).read())
     assert m and pld.pld_version() == int(m.group(1))
