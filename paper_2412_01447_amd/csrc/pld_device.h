@@ -473,8 +473,14 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
 // in which rows of width d stream, or (0, 0) past 8192 (row_dot, one row at a
 // time).  A piece holds a few narrow rows, four to eight loads per lane, else a whole
 // row, up to twelve loads: past that two pieces no longer fit the 128 registers
-// that keep four waves per SIMD (two 8-wave blocks per CU), and half a row is a
-// piece.  Measured as one-call
+// that keep four waves per SIMD (two 8-wave blocks per CU) in the drafting kernels,
+// and half a row is a piece.  The ranking kernels need more beside the rows: with
+// eleven and twelve loads three waves per SIMD are left (both rankings) or with
+// twelve alone (hidden states), which costs them less than the waits of the form
+// before (us per call, all loads of a row, then a wait | whole rows | half rows; 32 x
+// 16384 tokens, 360 occurrences each: d = 5632 29.0 | 26.9 | 25.8, with 16 heads 31.6 |
+// 31.1 | 29.5, with 64 39.7 | 37.8 | 38.1; 6144 31.3 | 29.0 | 28.2, 34.7 | 32.4 | 32.5,
+// 41.9 | 39.2 | 40.1).  Measured as one-call
 // drafting of 8 x 65536 tokens with 1600 occurrences each (us per step, whole
 // rows | half rows | all loads of one to four rows, then a wait): d = 512
 // 23.0 | - | 24.5, 1024 25.0 | - | 25.5, 2048 28.9 | - | 28.8, 3584 35.1 | - |

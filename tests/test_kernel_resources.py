@@ -33,15 +33,28 @@ def kernels(tmp_path_factory):
     return out
 
 
-def blocks_per_cu(k, dynamic_lds=0):
-    vgprs, _, lds, threads = k
-    waves_per_simd = min(8, VGPRS // ((vgprs + 7) // 8 * 8))
-    return min(waves_per_simd * 4 // (threads // 64), LDS // max(1, lds + dynamic_lds))
+def waves_per_simd(k):
+    return min(8, VGPRS // ((k[0] + 7) // 8 * 8))
+
+
+def blocks_per_cu(k):
+    return min(waves_per_simd(k) * 4 // (k[3] // 64), LDS // max(1, k[2]))
 
 
 def test_no_kernel_spills(kernels):
     assert len(kernels) > 50
     assert {n: k for n, k in kernels.items() if k[1]} == {}
+
+
+def test_waves_per_simd_of_the_row_forms(kernels):
+    """Four waves per SIMD wherever hidden rows are scored, but for the ranking kernels'
+    widest whole-row forms."""
+    rows = {n: waves_per_simd(k) for n, k in kernels.items()
+            if re.match("draft_kernel|draft_part_kernel|rank_hidden|rank_both", n)}
+    assert len(rows) > 80
+    assert {n: w for n, w in rows.items() if w < 4} == {
+        "rank_hidden_kernelILi1ELi12ELi4": 3, "rank_both_kernelILi1ELi11": 3,
+        "rank_both_kernelILi1ELi12": 3}
 
 
 def test_prompt_lookup_blocks_per_cu(kernels):
