@@ -991,25 +991,73 @@ def test_draft_fused_parity(case, split):
 
 @pytest.mark.parametrize("split", [64, 57, 240, 241, 1000])
 def test_draft_finish_read_ahead_limits(split):
-    """All-equal tokens make every position an occurrence.  4096 positions in
-    64 parts of 64 entries fill the finishing kernel's read-ahead exactly, as
-    do 240 parts (of 24; the most it covers); 57 parts of 72 hold more than it
-    reads per part, and 241 or 1000 parts are more than it covers: these take
-    the windowed compaction."""
+    """All-equal tokens make every position of 4096 an occurrence.  57 to 241 blocks
+    asked for are a team, which lists them itself; 1000 parts take the finishing
+    launch and its windowed compaction.  (Its read-ahead's limits:
+    test_draft_finish_limits.)"""
     test_draft_fused_parity((2, 4096, 1, 1, 1, 64, 0, 6, 13), split)
 
 
 @pytest.mark.parametrize("split", [192, 240, 241, 1000])
 def test_draft_finish_limits_past_the_team(split):
-    """The same limits where no team takes the call: 15360 positions, every one an
-    occurrence, in 240 parts of 64 (the read-ahead exactly), 192 of 80, 241 of 64
-    (more parts than it covers) and 1000 of 16."""
+    """The same over 15360 positions, two search passes: 192 to 241 blocks are a team of
+    at most 128 whose shares are long lists, 1000 parts of 16 are past the team."""
     test_draft_fused_parity((2, 15360, 1, 1, 1, 64, 0, 6, 14), split)
+
+
+@pytest.mark.parametrize("d,R", [(64, 0), (0, 5)])
+@pytest.mark.parametrize("split,most", [(240, 63), (240, 64), (240, 65), (241, 64), (1000, 20)])
+def test_draft_finish_limits(d, R, split, most, T=20480):
+    """The finishing launch past the lengths that a team takes: 240 parts are the most
+    its read-ahead covers and 64 entries the most it reads of one.  One part of `most`
+    entries among parts of none to twenty, the part after it empty; ragged and invalid
+    lengths; two calls on one workspace; the same bits as the separate calls."""
+    say("draft finish limits", d, R, split, most)
+    B, K = 3, 6
+    P = -(-(-(-T // split)) // 8) * 8                # positions per part
+    assert most < P
+    rng = np.random.default_rng(split + most + d)
+    toks = rng.integers(1, 1 << 20, size=(B, T)).astype(np.int32)
+    lens = np.array([T, T - 777, T + 1], np.int32)
+    for b in (0, 1):
+        for s in range(split):
+            n = most if s == 3 else 0 if s == 4 else int(rng.integers(0, min(P, 21)))
+            at = np.arange(max(s * P, 1), min((s + 1) * P, lens[b] - 1))
+            toks[b, rng.choice(at, min(n, len(at)), replace=False)] = 0
+        toks[b, lens[b] - 1] = 0
+    td, ld = d_i32(toks), d_i32(lens)
+    art = (d_bf16(synth.f32_to_bf16_bits(rng.standard_normal((B, T, d)).astype(np.float32))) if d
+           else d_f32(rng.random((B, R, T), dtype=np.float32)))
+    i32 = dict(dtype=torch.int32, device="cuda")
+    ws = draft_workspace(B, split)
+    for nmin, nmax in ((1, 1), (1, 2)):
+        cp, cc, nu = oracle.find(toks, lens, nmin, nmax)
+        if nmax == 1:
+            assert np.bincount(cp[0, :cc[0]] // P).max() == most
+        rsc, rbp, rbs = (gpu_rank_hidden(art, lens, cp, cc) if d else
+                         gpu_rank_attn(art, lens, cp, cc, pld.PLD_AGG_SUM))
+        o = [torch.full((B, T), -1, **i32), torch.zeros(B, **i32), torch.zeros(B, **i32),
+             torch.zeros(B, **i32), torch.zeros(B, dtype=torch.float32, device="cuda"),
+             torch.zeros((B, K), **i32), torch.zeros(B, **i32)]
+        sc = torch.zeros((B, T), dtype=torch.float32, device="cuda")
+        (pld.pld_draft_hidden if d else pld.pld_draft_attn)(
+            td, ld, nmin, nmax, art, K, *o, scores=sc, blocks_per_seq=split, workspace=ws)
+        torch.cuda.synchronize()
+        g = [t.cpu().numpy() for t in o]
+        check_find((g[0], g[1], g[2]), (cp, cc, nu), f"n{nmin}-{nmax}")
+        gs = sc.cpu().numpy()
+        for b in range(B):
+            assert np.array_equal(gs[b, :cc[b]], rsc[b, :cc[b]])
+        assert np.array_equal(g[3], rbp) and np.array_equal(g[4], rbs)
+        rd, rl = oracle.emit(toks, lens, rbp, K)
+        assert np.array_equal(g[5], rd) and np.array_equal(g[6], rl)
+        assert draft_keys_zero(ws, B)
 
 
 @pytest.mark.parametrize("d,R,total", [(512, 0, 64), (512, 0, 65), (512, 0, 1000), (4096, 0, 8),
                                        (4096, 0, 9), (4096, 0, 45), (8192, 0, 5), (9000, 0, 23),
-                                       (64, 0, 64), (64, 0, 65), (64, 0, 3000), (0, 5, 256), (0, 5, 257), (0, 70, 1000),
+                                       (64, 0, 64), (64, 0, 65), (64, 0, 3000), (0, 5, 256),
+                                       (0, 5, 257), (0, 70, 1000),
                                        (0, 3, 4094), (0, 5, 409), (0, 5, 410), (0, 70, 29),
                                        (0, 70, 30)])
 def test_draft_team(d, R, total, T=4096):
@@ -1077,8 +1125,9 @@ def test_draft_team_two_passes(T, d, R, total):
 
 @pytest.mark.parametrize("split", [192, 240, 241, 1000])
 def test_draft_finish_limits_small_share(split):
-    """The finishing launch's limits over four sequences, whose share of the GPU is too
-    small for a team at these splits."""
+    """All-equal tokens over four sequences of 15360 positions, whose share of the GPU is
+    too small for a team at these splits: parts of 64 and 80 entries, and of 64 in more
+    parts than the read-ahead covers."""
     test_draft_fused_parity((4, 15360, 1, 1, 1, 64, 0, 6, 14), split)
 
 
