@@ -513,8 +513,9 @@ int pld_accept_commit(const int32_t *draft, const int32_t *draft_len, int B, int
  *                   its own (not shared with the ranking or verification
  *                   calls), zero before the first call.  Its first B*128
  *                   bytes (the key slots) are left zero by every call; the
- *                   rest is per-block counts, rewritten by calls that use them.  Calls
- *                   that share one workspace must not overlap in time.
+ *                   rest is per-block counts, rewritten by calls that use them
+ *                   (so fill it with zeros again before a call of a larger B).
+ *                   Calls that share one workspace must not overlap in time.
  *   cand_pos, scores  entries past cand_count are unspecified on return.
  *   scores          may be NULL.
  * Errors: as the separate calls; S out of range, S = 1 with tok_stride > 8192

@@ -22,7 +22,8 @@ class DraftStep:
     """mode: "split" runs the separate calls (find, rank, emit), "fused" the one-call
     drafting (one ranking artifact), "auto" the one-call drafting when there is one
     ranking artifact and the separate calls otherwise.  draft_split is the one-call
-    drafting's blocks per sequence (1: one block owns a sequence, tok_stride <= 8192).
+    drafting's blocks per sequence (1: one block owns a sequence, tok_stride <= 8192;
+    more: up to as many share it).
     rank_both: with both artifacts, the two scorings share one launch (pld_score_both)
     instead of two (the same scores and choices)."""
 
@@ -172,13 +173,23 @@ class DraftStep:
     def tune_split(self, cand_count, hidden=True):
         """Blocks per sequence for the one-call drafting from observed candidate
         counts (e.g. the previous step's).  Short contexts with short lists keep
-        one block per sequence (one launch): up to 32 hidden rows or 256
-        attention gathers in the longest list (past 32 rows of 8 KB, spreading
-        them over more CUs repays the finishing launch).  Otherwise, for
-        hidden-state ranking, about 32 rows per block of the longest list and at
-        least 512 blocks in all (the library gives grids of up to 512 blocks 8
-        waves each, two per CU); for attention ranking, about 32 gathers per
-        block; and at least 64 positions per block."""
+        one block per sequence: up to 32 hidden rows or 256 attention candidates
+        in the longest list, whatever the rows' width and the number of heads.
+        Otherwise, for hidden-state ranking, about 32 rows per block of the
+        longest list and at least 512 blocks in all (the library gives split
+        grids of up to 512 blocks 8 waves each, two per CU); for attention
+        ranking, about 32 candidates per block; and at least 64 positions per
+        block.  Up to 16384 tokens the library then takes a team of up to that
+        many blocks, as a rule in one launch; past them, blocks of positions and
+        a finishing launch.
+
+        The limit of one block was set against blocks of positions.  Against a
+        team it is high for wide rows and many heads and low for narrow rows (us
+        per step, one block | a team of 64 or 8; 8 sequences of 2048 tokens, 16
+        and 32 rows: d = 2048 6.0 7.0 | 6.5 6.9, 4096 6.6 8.0 | 7.0 7.1, 8192 8.2
+        10.5 | 7.6 7.7; of 4096 tokens, 64 and 256 candidates: 16 heads 5.5 7.0 |
+        5.5 6.8, 64 heads 6.2 9.2 | 6.8 6.9); set_split or autotune_split chooses
+        otherwise."""
         import math
         mx = int(max(int(c) for c in cand_count)) if len(cand_count) else 0
         small = 32 if hidden else 256
@@ -308,8 +319,10 @@ class DraftStep:
     def plan(self, tokens, lens, logits, hidden=None, attn=None, ngram=(1, 1), agg=PLD_AGG_SUM,
              threshold=float("-inf"), prefix_match=None, commit=None, stream=None):
         """The step as an ordered list of (name, prepared call), one kernel per entry
-        except "find" and prompt lookup's "draft" on long contexts: the same work as run(), with every
-        argument marshalled once so that issuing a step costs only the launches.
+        except where "find" (past 16384 tokens), the one-call "draft" past its team and
+        prompt lookup's "draft" past one launch take several: the same work as run(),
+        with every argument marshalled once so that issuing a step costs only the
+        launches.
         commit=(limit, stats) adds the commit of the generation loop (with greedy
         verification, fused into the acceptance's launch: pld_accept_commit)."""
         P = dict(stream=stream, prepare=True)
