@@ -26,10 +26,10 @@ constexpr int kPrefixChunk = 16;      // tokens compared per trip to memory (at 
 constexpr int kPrefixChunkLds = 4;    // and to LDS
 // Sequences up to which rows of 8193 to 16384 tokens take one launch.  Their tokens
 // and list leave a CU room for one block (131 KB of LDS), where the find call's has
-// two: past that short lists are faster as find and selection (us per step, the three
+// two: past that short lists are faster as find and selection (us per call, the three
 // separate calls | one launch | two; 4, 256 and 2048 occurrences each): 1024 x 16384
-// 25.9 32.4 54.7 | 24.9 25.7 31.1 | 23.4 28.6 37.2, 2048 x 16384 46.7 58.7 97.5 | 50.5
-// 52.6 62.9 | 45.4 54.6 74.4.
+// 25.9 32.4 55.2 | 24.1 25.4 30.9 | 23.2 27.5 36.0, 2048 x 16384 46.6 58.5 97.9 | 49.3
+// 51.9 62.0 | 43.9 52.2 66.9.
 constexpr int kDraftOneLaunchB = 1024;
 
 struct PrefixArgs {
@@ -71,14 +71,19 @@ __device__ __forceinline__ bool match_chunk(const int32_t *x, int64_t j, int lim
 #pragma unroll
         for (int k = 0; k < kChunk; ++k) v[k] = x[max(at - k, (int64_t)0)];
     }
-    const int m0 = m;
-    bool run = true;
+    // The query's tokens are requested together, not each once the one before has
+    // matched: four trips to LDS one after the other bound long matches (us per call,
+    // one by one | together; every occurrence matching 64 tokens: 64 x 8192, 200 each,
+    // in LDS 10.0 | 7.7, 64 x 20000, 500 each, in memory 18.7 | 15.2).
+    int32_t q[kChunk];
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) {
-        run = run && m0 + k < lim && v[k] == query(m0 + k);
-        m += run ? 1 : 0;
-    }
-    return run;
+    for (int k = 0; k < kChunk; ++k) q[k] = query(m + k);
+    uint32_t same = 0;
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) same |= (v[k] == q[k] ? 1u : 0u) << k;
+    const int n = min(__builtin_ctz(~same), lim - m);   // kChunk <= 16: ~same has a bit
+    m += n;
+    return n == kChunk;
 }
 
 // The match length of candidate j (0 <= j <= T-2), kChunk tokens at a time, x in
@@ -86,8 +91,9 @@ __device__ __forceinline__ bool match_chunk(const int32_t *x, int64_t j, int lim
 // lanes' scattered reads of memory is the addresses that a CU's load path takes,
 // about one a clock: 16 tokens in four 16-byte loads, not sixteen (4 x 100000
 // tokens, 2500 occurrences: 40.5 -> 26.5 us per step).  In LDS most candidates
-// end within four tokens (per step, 16 | 8 | 4 at a time: 8 x 4096 tokens 14.3 | 14.7 |
-// 14.0 us, 48 x 16384 29.3 | 28.8 | 28.2).
+// end within four tokens (us per call, 16 | 8 | 4 at a time: 8 x 4096 tokens, 64
+// occurrences each 4.7 | 4.5 | 4.3, 48 x 16384, 256 each 6.6 | 6.2 | 6.0; where every
+// one of 200 matches 64 tokens, 64 x 8192, 7.6 | 7.4 | 7.7).
 template <int kChunk, bool kGlobal, class QueryToken>
 __device__ __forceinline__ int match_length(const int32_t *x, int64_t j, int qn, QueryToken query) {
     // the run can reach back to x[0] and no further than the query suffix
@@ -163,10 +169,9 @@ struct DraftPrefixArgs {
 // One block per sequence, tok_stride <= kPasses * kFindFusedMax: the search of the
 // one-block find, its list in LDS as well, then a lane per candidate.  With one pass
 // two blocks share a CU (66 KB of LDS each; up to 64 registers, eight waves per
-// SIMD), which is what bounds large batches (us per step, the three separate calls |
-// 67 registers, one block per CU | two; 128 occurrences or fewer): 512 x 8192 14.6 |
-// 9.8 | 7.9, 4096 x 8192 64.4 | 59.5 | 40.7, 4096 x 1024 34.7 | 38.1 | 26.3, 16384 x 512
-// 115 | 141 | 93.
+// SIMD), which is what bounds large batches (us per call, the three separate calls |
+// one block per CU | two; 128 occurrences or fewer): 512 x 8192 14.5 | 9.4 | 7.7, 4096 x
+// 8192 64.0 | 57.3 | 39.8, 4096 x 1024 34.6 | 36.2 | 25.8, 16384 x 512 115 | 134 | 91.
 template <int kPasses>
 __global__ __launch_bounds__(kPrefixThreads, kPasses == 1 ? 8 : 4) void draft_prefix_kernel(DraftPrefixArgs d) {
     static_assert(kPrefixWaves == kFindWavesFused, "the search takes the whole block");
@@ -217,14 +222,12 @@ __global__ __launch_bounds__(kPrefixThreads, kPasses == 1 ? 8 : 4) void draft_pr
 // Up to 256 sequences there is a CU for each, and 1024 threads make the few thousand
 // candidates of a long context few dependent rounds (position, tokens); up to 512,
 // two blocks of 512 threads share one.  Past that what bounds the call is how many
-// short lists a CU takes at once: 256 threads, whose 8-token chunks need fewer
-// registers than 16 (4 | 8 | 16 tokens in the 1024-thread form, 4 x 100000 tokens,
-// every one of 2500 occurrences matching 64: 24.3 | 20.9 | 18.8 us).  Measured (us per
-// call, 1024 threads | 512 | 256 of 16-token chunks | 256 of 8): 256 x 16384 tokens, 256
-// occurrences each 4.6 | 4.4 | 5.2 | -, 2048 each 7.9 | 9.6 | 12.8 | -; 512 x 4096, 4 each
-// 5.4 | 3.9 | 3.7 | -, 512 x 16384, 2048 each 13.5 | 10.9 | 14.7 | -; 2048 x 4096, 64
-// each 22.9 | 10.6 | 7.4 | 6.1, 4096 x 4096, 4 each 34.1 | 14.4 | 7.8 | 6.5, 65535 x 128, 8
-// each 646 | 231 | 98 | 77.
+// short lists a CU takes at once: 256 threads, whose 8-token chunks need half the
+// registers of 16 (28, not 60).  Measured (us per call, 1024 threads | 512 | 256 of
+// 16-token chunks | 256 of 8): 256 x 16384 tokens, 256 occurrences each 5.0 | 5.0 | 5.5 |
+// 5.2, 2048 each 7.1 | 8.0 | 11.0 | 10.5; 512 x 4096, 4 each 4.2 | 3.7 | 4.2 | 3.7, 512 x
+// 16384, 2048 each 9.6 | 10.1 | 12.3 | 11.8; 2048 x 4096, 64 each 13.3 | 8.8 | 6.4 | 6.0,
+// 4096 x 4096, 4 each 18.1 | 11.1 | 6.7 | 6.3, 65535 x 128, 8 each 330 | 189 | 79 | 71.
 static void launch_select_prefix(const PrefixArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)a.B);
     if (a.B <= 256)
