@@ -488,10 +488,12 @@ __device__ __forceinline__ void stream_rows(int n, int nch, RowPtr row, const ui
 // 7168 51.3 | 53.2 | 53.0, 8192 55.8 | 56.0 | -; but 44 x 16917 tokens with few
 // occurrences, d = 7168, take 39.2 | 35.6 | 35.6, the blocks no longer resident
 // together.  Few rows to a piece keep the rows of a short list from waiting for each
-// other: d = 512 in one block per sequence, 8 x 2048 tokens with 16, 64 and 512
-// occurrences each, load-all-then-wait 6.7 8.5 32.1 | eight rows 8.3 9.8 32.8 | four
-// 5.8 7.8 29.1 | two 5.4 7.5 28.8, and the ranking call alone, 8 x 8192 with 512 each, 9.4 |
-// 11.8 | 9.3 | 9.6; d = 1024 6.9 8.9 36.0 | - | four 6.2 8.6 33.3 | two 5.6 8.1 32.8.
+// other, more rows keep a long one's loads in flight.  us per call: d = 512 in one block
+// per sequence, 8 x 2048 tokens with 16, 64 and 512 occurrences each, load-all-then-wait
+// 6.7 8.5 32.1 | eight rows 8.3 9.8 32.8 | four 5.8 7.8 29.1 | two 5.4 7.5 28.8, and the
+// ranking call alone, 8 x 8192 with 512 each, 9.4 | 11.8 | 9.3 | 9.6; d = 1024 6.9 8.9 36.0 |
+// four 6.0 8.4 33.2 | three 5.8 8.4 33.0 | two 5.6 8.1 32.8, both rankings with 16 heads,
+// 256 x 1024 with 128 each, 22.7 | 23.4 | 22.5 | 24.1.
 template <class F>
 inline void with_row_form(int d, F f) {
     using std::integral_constant;
@@ -499,7 +501,7 @@ inline void with_row_form(int d, F f) {
     return f(integral_constant<int, rows>{}, integral_constant<int, loads>{})
     switch ((d + 511) / 512) {   // 16-byte loads per lane and row
     case 1: PLD_ROW_FORM(4, 1);
-    case 2: PLD_ROW_FORM(2, 2);
+    case 2: PLD_ROW_FORM(3, 2);
     case 3: PLD_ROW_FORM(2, 3);
     case 4: PLD_ROW_FORM(2, 4);
     case 5: PLD_ROW_FORM(1, 5);

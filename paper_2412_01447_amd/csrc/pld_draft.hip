@@ -123,7 +123,7 @@ __device__ void draft_score_rows(const DraftArgs &a, int b, int64_t T, bool seq_
     if constexpr (kLoads > 0) {
         // The query's norm under the first loads' latency, unless each of sixteen
         // waves has a row: their loads then fill the CU's path for longer than the
-        // norm takes, and it is ready sooner before them (us per step after the loads
+        // norm takes, and it is ready sooner before them (us per call after the loads
         // | before; 8 x 2048 tokens, one block each, 16 and 32 rows: d = 1024 5.6 6.5 |
         // 5.5 6.3, 4096 6.9 8.6 | 6.6 8.1, 8192 8.5 10.7 | 8.1 10.5; blocks of a team, 4
         // to 8 rows: 12 x 3333, d = 4096 7.7 | 7.7, 8192 8.6 | 9.1, 16 x 8192, 8192
@@ -209,9 +209,9 @@ __device__ void write_draft(const DraftArgs &a, int b, int64_t T, bool tok_ok, u
 // 30, d = 8192 13.9 | 13.2 | 12.7, 1 x 8192, 800, d = 4096 13.9 | 13.9 | 14.6 (the
 // split form: 17.0, 18.4, 15.9, 17.2); scored by one block up to 64 KB, against
 // 128 KB: the same or faster.  What bounds narrow rows is their reductions, not
-// their bytes, so a block scores no more than 64 of them alone (8 x 8192 tokens, 256
-// occurrences, d = 64: up to 64 KB 17.7, up to 64 rows 8.1, the split form 11.1; one
-// block takes 6.7 for 32 rows, 7.9 for 64 and 11.6 for 128).
+// their bytes, so a block scores no more than 64 of them alone (us per call, 8 x 8192
+// tokens, 256 occurrences, d = 64: up to 64 KB 17.7, up to 64 rows 8.1, the split form
+// 11.1; one block takes 6.7 for 32 rows, 7.9 for 64 and 11.6 for 128).
 // Attention's scattered weights each take an address of the CU's load path, and few
 // of their lines are in flight per CU, so a sequence is one block's up to 2048
 // weights, not up to a number of candidates (up to 256 candidates | 2048 weights, us
@@ -232,7 +232,7 @@ constexpr int kAloneRows = 64;            // hidden: rows that one block scores 
 // Sequences from which they lie along x of the grid, the teams along y.  Blocks go
 // round the 8 XCDs in turn, so a batch that is a multiple of 8 then has each team
 // within one XCD, whose L2 fetches its token row once; with the teams along x every
-// XCD fetches every row (us per step, split | teams along x | sequences along x; 32
+// XCD fetches every row (us per call, split | teams along x | sequences along x; 32
 // heads): 32 x 16384 tokens, 20 occurrences 9.5 | 10.3 | 7.0, 100 each 11.3 | 12.3 | 9.6,
 // 600 each 16.3 | 17.4 | 16.0, 16 x 16384, 100 each 9.6 | 9.8 | 8.4; over 900 shapes of 8
 // to 256 sequences 8% less in the mean and at most 4% more.  Below 8 it only gathers
@@ -751,8 +751,8 @@ static void launch_draft_as(const DraftArgs &a, hipStream_t s) {
     // hidden, 16 x 8192 (S 34, fit 16) 25.9 | 28.7, 24 x 8192 (S 37, fit 10) 35.8 |
     // 32.0; attention, 16 x 8192 (S 34, fit 16) 17.4 | 20.3, 24 x 4000 (S 24, fit 10)
     // 17.3 | 20.5, 32 x 8192 (S 40, fit 8) 26.3 | 27.6, 48 x 4000 (S 19, fit 5) 22.7 |
-    // 26.0, 64 x 16384 (S 24, fit 4) with 12 occurrences each 7.2 | 12.0, but with 600 each
-    // 26.0 | 24.3; two attention blocks per CU (64 registers): 12 x 3000 14.8 -> 16.6, 24 x 4000
+    // 26.0 (us per call: 64 x 16384, S 24, fit 4, 12 occurrences each 7.2 | 12.0, but 600
+    // each 26.0 | 24.3); two attention blocks per CU (64 registers): 12 x 3000 14.8 -> 16.6, 24 x 4000
     // 17.3 -> 18.6.
     const bool one = a.tok_stride <= kFindFusedMax;   // search passes
     void (*const kernel)(DraftArgs) = one ? &draft_kernel<kHidden, kRows, kLoads, 1>

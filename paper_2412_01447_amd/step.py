@@ -185,7 +185,7 @@ class DraftStep:
 
         The limit of one block was set against blocks of positions.  Against a
         team it is high for wide rows and many heads and low for narrow rows (us
-        per step, one block | a team of 64 or 8; 8 sequences of 2048 tokens, 16
+        per call, one block | a team of 64 or 8; 8 sequences of 2048 tokens, 16
         and 32 rows: d = 2048 6.0 7.0 | 6.5 6.9, 4096 6.6 8.0 | 7.0 7.1, 8192 8.2
         10.5 | 7.6 7.7; of 4096 tokens, 64 and 256 candidates: 16 heads 5.5 7.0 |
         5.5 6.8, 64 heads 6.2 9.2 | 6.8 6.9); set_split or autotune_split chooses
