@@ -229,15 +229,16 @@ constexpr int kTeamPasses = 2;            // search passes of the longest rows, 
 constexpr size_t kTeamQueryMax = 163840 - 2 * 4 * kTeamPasses * kFindFusedMax - 1024;
 constexpr int kTeamBytes = 65536;         // hidden: rows' bytes per block, 4 to 8 rows
 constexpr int kAloneRows = 64;            // hidden: rows that one block scores alone, at most
-// Sequences from which they lie along x of the grid, the teams along y.  Blocks go
-// round the 8 XCDs in turn, so a batch that is a multiple of 8 then has each team
-// within one XCD, whose L2 fetches its token row once; with the teams along x every
-// XCD fetches every row (us per call, split | teams along x | sequences along x; 32
-// heads): 32 x 16384 tokens, 20 occurrences 9.5 | 10.3 | 7.0, 100 each 11.3 | 12.3 | 9.6,
-// 600 each 16.3 | 17.4 | 16.0, 16 x 16384, 100 each 9.6 | 9.8 | 8.4; over 900 shapes of 8
-// to 256 sequences 8% less in the mean and at most 4% more.  Below 8 it only gathers
-// a team's scattered loads on fewer XCDs (4 x 16384, 600 each - | 8.6 | 9.6).
-constexpr int kTeamSeqXB = 8;
+// The sequences lie along x of the grid, the teams along y.  Blocks go round the 8
+// XCDs in turn, so a batch that is a multiple of 8 then has each team within one XCD,
+// whose L2 fetches its token row once; with the teams along x every XCD fetches
+// every row (us per call, split | teams along x | sequences along x; 32 heads): 32 x
+// 16384 tokens, 20 occurrences 9.5 | 10.3 | 7.0, 100 each 11.3 | 12.3 | 9.6, 600 each 16.3 |
+// 17.4 | 16.0, 16 x 16384, 100 each 9.6 | 9.8 | 8.4; over 900 shapes of 8 to 256 sequences
+// 8% less in the mean and at most 4% more.  Attention's teams of fewer sequences
+// lie along x: 4 x 16384, 600 each - | 8.6 | 9.6.  (A kernel that chooses at run time
+// takes 0.2 us more with one block: 1 x 1024, 50 heads 7.2 | 7.4.)
+constexpr int kTeamXMaxB = 7;
 constexpr int kAloneGathers = 2048, kTeamGathers = 32;   // attention: weights; candidates
 // Blocks of a team of `most` that share the scoring of `total` candidates.
 template <bool kHidden>
@@ -250,8 +251,9 @@ __device__ __forceinline__ int team_size(const DraftArgs &a, int total, int most
     return min(most, (total + share - 1) / share);
 }
 
-// kPasses search passes: tok_stride <= kPasses * kFindFusedMax.
-template <bool kHidden, int kRows, int kLoads, int kPasses>
+// kPasses search passes: tok_stride <= kPasses * kFindFusedMax.  kTeamX: the teams
+// along x of the grid, the sequences along y.
+template <bool kHidden, int kRows, int kLoads, int kPasses, bool kTeamX>
 __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArgs a) {
     constexpr int kWaves = kFindWavesFused;
     constexpr int kThreads = kWaves * kWave;
@@ -260,8 +262,7 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
     extern __shared__ uint4 s_q[];                           // query row H[T-2] (hidden)
     __shared__ int s_lvl[kWaves][kMaxNgram];
     __shared__ uint64_t s_key[kWaves];
-    const bool seq_x = a.B >= kTeamSeqXB;
-    const int b = seq_x ? blockIdx.x : blockIdx.y, part = seq_x ? blockIdx.y : blockIdx.x;
+    const int b = kTeamX ? blockIdx.y : blockIdx.x, part = kTeamX ? blockIdx.x : blockIdx.y;
     const int w = threadIdx.x / kWave;
     const int32_t *x = a.tokens + (int64_t)b * a.tok_stride;
 
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(kFindWavesFused * kWave) void draft_kernel(DraftArg
         a.cand_count[b] = total;
         a.ngram_used[b] = n_used;
     }
-    const int team = team_size<kHidden>(a, total, (int)(seq_x ? gridDim.y : gridDim.x));
+    const int team = team_size<kHidden>(a, total, (int)(kTeamX ? gridDim.x : gridDim.y));
     if (part >= team) return;   // block-uniform
     uint64_t best = 0;
     if (total > 0) {   // block-uniform
@@ -755,8 +756,8 @@ static void launch_draft_as(const DraftArgs &a, hipStream_t s) {
     // each 26.0 | 24.3); two attention blocks per CU (64 registers): 12 x 3000 14.8 -> 16.6, 24 x 4000
     // 17.3 -> 18.6.
     const bool one = a.tok_stride <= kFindFusedMax;   // search passes
-    void (*const kernel)(DraftArgs) = one ? &draft_kernel<kHidden, kRows, kLoads, 1>
-                                          : &draft_kernel<kHidden, kRows, kLoads, kTeamPasses>;
+    void (*kernel)(DraftArgs) = one ? &draft_kernel<kHidden, kRows, kLoads, 1, false>
+                                    : &draft_kernel<kHidden, kRows, kLoads, kTeamPasses, false>;
     int team = a.S == 1 ? 1 : 0;
     if (a.S > 1 && a.tok_stride <= kTeamPasses * kFindFusedMax &&
         (one || lds <= kTeamQueryMax)) {
@@ -768,8 +769,14 @@ static void launch_draft_as(const DraftArgs &a, hipStream_t s) {
         }
     }
     if (team > 0) {
-        hipLaunchKernelGGL(kernel, a.B >= kTeamSeqXB ? dim3(a.B, team) : dim3(team, a.B),
-                           dim3(kFindWavesFused * kWave), lds, s, a);
+        dim3 grid(a.B, team);
+        if constexpr (!kHidden)
+            if (team > 1 && a.B <= kTeamXMaxB) {
+                kernel = one ? &draft_kernel<kHidden, kRows, kLoads, 1, true>
+                             : &draft_kernel<kHidden, kRows, kLoads, kTeamPasses, true>;
+                grid = dim3(team, a.B);
+            }
+        hipLaunchKernelGGL(kernel, grid, dim3(kFindWavesFused * kWave), lds, s, a);
         return;
     }
     if (a.nmin < a.nmax)
