@@ -1131,6 +1131,48 @@ def test_draft_finish_limits_small_share(split):
     test_draft_fused_parity((4, 15360, 1, 1, 1, 64, 0, 6, 14), split)
 
 
+@pytest.mark.parametrize("T", [3000, 9000])
+@pytest.mark.parametrize("B", [7, 8, 9])
+@pytest.mark.parametrize("d,R", [(1024, 0), (0, 50)])
+def test_draft_team_batches(d, R, B, T):
+    """Teams of the batches at which attention's grid changes its order, with one and two
+    search passes: lists of none to several blocks' shares, ragged lengths; the same
+    bits as the separate calls."""
+    say("draft team batches", d, R, B, T)
+    rng = np.random.default_rng(B + T + d)
+    K, S = 5, 6
+    toks = rng.integers(1, 1 << 20, size=(B, T)).astype(np.int32)
+    lens = rng.integers(T // 2, T + 1, size=B).astype(np.int32)
+    for b in range(B):
+        n = int(rng.integers(0, 250)) if b else 200
+        toks[b, 1 + rng.choice(lens[b] - 2, n, replace=False)] = 0
+        toks[b, lens[b] - 1] = 0
+    art = (d_bf16(synth.f32_to_bf16_bits(rng.standard_normal((B, T, d)).astype(np.float32))) if d
+           else d_f32(rng.random((B, R, T), dtype=np.float32)))
+    cp, cc, nu = oracle.find(toks, lens, 1, 1)
+    rsc, rbp, rbs = (gpu_rank_hidden(art, lens, cp, cc) if d else
+                     gpu_rank_attn(art, lens, cp, cc, pld.PLD_AGG_SUM))
+    i32 = dict(dtype=torch.int32, device="cuda")
+    ws = draft_workspace(B, S)
+    for _ in range(2):
+        o = [torch.full((B, T), -1, **i32), torch.zeros(B, **i32), torch.zeros(B, **i32),
+             torch.zeros(B, **i32), torch.zeros(B, dtype=torch.float32, device="cuda"),
+             torch.zeros((B, K), **i32), torch.zeros(B, **i32)]
+        sc = torch.zeros((B, T), dtype=torch.float32, device="cuda")
+        (pld.pld_draft_hidden if d else pld.pld_draft_attn)(
+            d_i32(toks), d_i32(lens), 1, 1, art, K, *o, scores=sc, blocks_per_seq=S, workspace=ws)
+        torch.cuda.synchronize()
+        g = [t.cpu().numpy() for t in o]
+        check_find((g[0], g[1], g[2]), (cp, cc, nu), "team")
+        gs = sc.cpu().numpy()
+        for b in range(B):
+            assert np.array_equal(gs[b, :cc[b]], rsc[b, :cc[b]])
+        assert np.array_equal(g[3], rbp) and np.array_equal(g[4], rbs)
+        rd, rl = oracle.emit(toks, lens, rbp, K)
+        assert np.array_equal(g[5], rd) and np.array_equal(g[6], rl)
+        assert draft_keys_zero(ws, B)
+
+
 def test_autotune_split_keeps_the_results():
     """DraftStep.autotune_split times a few blocks-per-sequence choices (8-wave
     blocks for small grids, 4-wave blocks for large ones) and keeps one; the
